@@ -315,9 +315,11 @@ zarya_status zarya_slot_attn_plan(const zarya_slot_attn_desc* desc, zarya_slot_a
   if (st != ZARYA_OK) return st;
   const AttnPlan pl = plan_attn(desc);
   if (desc->dtype == ZARYA_DTYPE_F32) {
+    const int64_t groups = (int64_t)desc->batch * desc->n_kv_heads;
+    const int rows = attn_f32_rows_per_block(groups, pl.R, (int64_t)desc->prefix_len + pl.T);
     info->prefix_splits = 1;
-    info->rows_per_workgroup = kAttnF32RowsPerBlock;
-    info->workgroups = (int32_t)((pl.rows_total + kAttnF32RowsPerBlock - 1) / kAttnF32RowsPerBlock);
+    info->rows_per_workgroup = rows;
+    info->workgroups = (int32_t)(groups * ((pl.R + rows - 1) / rows));
     info->kernels = 1;
     return ZARYA_OK;
   }

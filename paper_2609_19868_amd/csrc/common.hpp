@@ -37,6 +37,24 @@ __device__ __forceinline__ f32x16 mfma32x32x16(const bf16x8& a, const bf16x8& b,
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+__device__ __forceinline__ f32x4 mfma16x16x4_f32(float a, float b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f32x16 mfma32x32x2_f32(float a, float b, const f32x16& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
+// Four consecutive floats at an address that is a multiple of 4 bytes (global
+// dwordx4 accesses need no more).
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ f32x4 load_f32x4(const float* p) {
+  return __builtin_bit_cast(f32x4, *reinterpret_cast<const f32x4_a4*>(p));
+}
+__device__ __forceinline__ void store_f32x4(float* p, const f32x4& v) {
+  *reinterpret_cast<f32x4_a4*>(p) = __builtin_bit_cast(f32x4_a4, v);
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 typedef __attribute__((address_space(3))) void* lds_ptr;
@@ -47,6 +65,11 @@ typedef __attribute__((address_space(3))) void* lds_ptr;
 // from emitting that template's host-side launch stub.
 __device__ __forceinline__ void dma16(const void* src, void* lds_base) {
   __builtin_amdgcn_global_load_lds(src, (lds_ptr)lds_base, 16, 0, 0);
+}
+
+// The same for 4 bytes per lane (lane l's bytes land at lds_base + 4*l).
+__device__ __forceinline__ void dma4(const void* src, void* lds_base) {
+  __builtin_amdgcn_global_load_lds(src, (lds_ptr)lds_base, 4, 0, 0);
 }
 
 // Buffer resource of `bytes` (< 4 GiB) bytes at `base` for raw byte-offset

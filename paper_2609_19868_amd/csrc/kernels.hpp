@@ -161,9 +161,15 @@ int64_t mask_budget_plan(int32_t n_masked, int32_t n_steps, double alpha0, uint6
 constexpr int kAppendMaxTokens = 8192;
 
 constexpr int kAttnKeysPerTile = 64;
-constexpr int kAttnF32RowsPerBlock = 32;    // float32 path: query rows per workgroup (D/16 lanes each)
+constexpr int kAttnF32Waves = 8;            // float32 path: waves per workgroup, which split the keys
 constexpr int kAttnRowsPerBlock = 128;      // four waves
 constexpr int kAttnWideRowsPerBlock = 256;  // eight waves: every K/V tile staged once for 256 rows
+// float32 path: query rows per workgroup.  32 rows read each key half as often
+// as 16; 16 rows make twice as many workgroups, which pays where 32 leave
+// compute units idle and every wave still walks more than one 16-key tile.
+constexpr int attn_f32_rows_per_block(int64_t groups, int64_t rows_per_group, int64_t keys) {
+  return groups * ((rows_per_group + 31) / 32) < 256 && keys > 16 * kAttnF32Waves ? 16 : 32;
+}
 // Tile configuration of the bf16 LM-head reduction (measured on MI355X over
 // the 0.6B/1.7B/4B shapes): 8 waves over a 256 x 256 tile, 64-deep stages,
 // three W and two hidden LDS buffers (160 KB), one workgroup per compute

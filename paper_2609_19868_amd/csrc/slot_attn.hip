@@ -491,65 +491,260 @@ __global__ __launch_bounds__(256) void slot_attn_merge_kernel(const float* __res
   if (lse && c == 0) lse[row] = (mx + __log2f(wsum)) * kLn2;
 }
 
-// float32 path: LPR = D/16 lanes per query row, each holding 16 elements of
-// the row's q and output; a score is the lanes' partial dot products summed
-// across the group (then taken from the group's first lane, so every lane
-// of a row follows the same online softmax, with expf).  Plain FMA
-// arithmetic; serves small float32 problems and every mask variant.
-template <int D>
-__global__ __launch_bounds__(kAttnF32RowsPerBlock * (D / 16)) void slot_attn_f32_kernel(AttnParams32 p) {
-  constexpr int LPR = D / 16;  // lanes per row
-  static_assert(LPR >= 1 && (LPR & (LPR - 1)) == 0 && 64 % LPR == 0, "a row's lanes are a power of two in a wave");
-  const int sub = threadIdx.x % LPR;  // this lane's 16-element slice of the row
-  const int gid = blockIdx.x * kAttnF32RowsPerBlock + threadIdx.x / LPR;
-  const bool row_ok = gid < p.rows_total;
-  // lanes past the last row follow a valid row (the shuffles need every lane
-  // of a group) and store nothing
-  const int grow = row_ok ? gid : p.rows_total - 1;
-  const int t = grow % p.T;
-  const int h = (grow / p.T) % p.Hq;
-  const int b = grow / (p.T * p.Hq);
-  const int g = h / p.G;
-  const int s = t / p.L, r = t - s * p.L;
-  const int pass = p.slot_pass ? (int)p.slot_pass[b * p.S + s] : p.pass;
-  const int vis_hi = s * p.L + (pass == 0 ? p.L : r + 1);
-  const int vis_lo = p.cross ? 0 : s * p.L;
-  const int lead = (int)(threadIdx.x % 64) & ~(LPR - 1);  // the group's first lane in the wave
+// float32 path.  One workgroup = 8 waves = 16 * NR query rows of one GQA group
+// (token-major, as above); the waves share the rows and split the keys: wave w
+// takes the 16-key tiles w, w + 8, ... of the prefix and the draft tokens and
+// keeps its own online softmax; the eight partials meet in LDS and are merged
+// in wave order, so no workspace and no second launch is needed.
+//
+// The products are v_mfma_f32_16x16x4_f32 (float32 operands and accumulators).
+// S^T = K Q^T leaves a lane the scores of one query row and four keys, which
+// are the B operands of O^T += V^T P^T as they stand.  The order of the
+// contraction and of the output rows is free, so K, Q and V are read straight
+// from global memory in 16-byte pieces, one per four MFMAs; nothing is staged:
+// the rows of a workgroup share each key through its waves' registers, and a
+// group's workgroups meet in one XCD's L2.
+//
+// Bound by the float32 matrix rate of the compute units that have rows: B = 2,
+// 16/8 heads, D = 128, 1000 + 64 keys, 64 tokens (128 workgroups of 16 rows)
+// takes 33 us, 32 TFLOP/s; one key at a time with a shuffled dot product per
+// row, as it was before, took 771 us.
+template <int D, int NR>
+__global__ __launch_bounds__(kAttnF32Waves * 64) __attribute__((amdgpu_waves_per_eu(2))) void slot_attn_f32_kernel(
+    AttnParams32 p) {
+  constexpr int NW = kAttnF32Waves;
+  constexpr int RB = 16 * NR;   // query rows per workgroup
+  constexpr int NKS = D / 16;   // 16-byte pieces of a K row per lane
+  constexpr int NC = D / 64;    // 16-byte pieces of a V row per lane
+  constexpr int NOB = D / 16;   // 16-wide blocks of the output: block 4 * c + e holds d = 64 * c + 4 * i + e
+  constexpr int OSTR = D + 4;   // row stride of the partial outputs in LDS
+  __shared__ __attribute__((aligned(16))) float part_o[NW][RB][OSTR];
+  __shared__ __attribute__((aligned(16))) float qs[RB][OSTR];  // scaled queries; the padding spreads the rows over the banks
+  __shared__ float part_m[NW][RB], part_l[NW][RB];
 
-  float qv[16], o[16];
-  const float* qrow = p.q + (size_t)grow * D + sub * 16;
-#pragma unroll
-  for (int d = 0; d < 16; ++d) {
-    qv[d] = qrow[d] * p.scale;
-    o[d] = 0.f;
-  }
-  float m = -INFINITY, l = 0.f;
-  auto visit = [&](const float* krow, const float* vrow) {
-    float part = 0.f;
-#pragma unroll
-    for (int d = 0; d < 16; ++d) part = fmaf(qv[d], krow[sub * 16 + d], part);
-#pragma unroll
-    for (int off = LPR / 2; off > 0; off >>= 1) part += __shfl_xor(part, off);
-    const float sc = __shfl(part, lead);
-    const float m_new = fmaxf(m, sc);
-    const float c = expf(m - m_new);
-    const float e = expf(sc - m_new);
-    l = l * c + e;
-#pragma unroll
-    for (int d = 0; d < 16; ++d) o[d] = fmaf(e, vrow[sub * 16 + d], o[d] * c);
-    m = m_new;
-  };
-  const size_t cbase = ((size_t)b * p.Hkv + g) * p.C * D;
+  const int n_rb = (p.G * p.T + RB - 1) / RB;
+  const int w = xcd_work_index(blockIdx.x, gridDim.x >> 3, p.B * p.Hkv * n_rb);
+  if (w < 0) return;
+  const int rb = w % n_rb, bg = w / n_rb;
+  const int b = bg / p.Hkv;
+  const int R = p.G * p.T;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 15, q4 = lane >> 4;
   const int Pb = p.prefix_lens ? min(max(p.prefix_lens[b], 0), p.P) : p.P;
-  for (int j = 0; j < Pb; ++j) visit(p.k_cache + cbase + (size_t)j * D, p.v_cache + cbase + (size_t)j * D);
-  const size_t sbase = ((size_t)b * p.Hkv + g) * p.T * D;
-  for (int j = vis_lo; j < vis_hi; ++j) visit(p.k_slot + sbase + (size_t)j * D, p.v_slot + sbase + (size_t)j * D);
-  if (!row_ok) return;
-  float* orow = p.out + (size_t)gid * D + sub * 16;
-  const float inv = 1.f / l;
+
+  // this lane's query rows (one per row tile) and their visible draft keys;
+  // rows past the end follow the last one and are not stored
+  int vis_lo[NR], vis_hi[NR];
 #pragma unroll
-  for (int d = 0; d < 16; ++d) orow[d] = o[d] * inv;
-  if (p.lse && sub == 0) p.lse[gid] = m + logf(l);
+  for (int r = 0; r < NR; ++r) {
+    const int row = min(rb * RB + 16 * r + n, R - 1);
+    const int t = row / p.G, s = t / p.L;
+    const int pass = p.slot_pass ? (int)p.slot_pass[b * p.S + s] : p.pass;
+    vis_hi[r] = pass == 0 ? (s + 1) * p.L : t + 1;
+    vis_lo[r] = p.cross ? 0 : s * p.L;
+  }
+  for (int x = threadIdx.x; x < RB * (D / 4); x += NW * 64) {
+    const int lr = x / (D / 4), c = 4 * (x % (D / 4));
+    const int row = min(rb * RB + lr, R - 1);
+    const size_t qr = (size_t)bg * R + (size_t)(row % p.G) * p.T + row / p.G;
+    *reinterpret_cast<f32x4*>(&qs[lr][c]) = load_f32x4(p.q + qr * D + c) * p.scale;
+  }
+  __syncthreads();
+  const uint32_t q_addr = lds_addr(&qs[n][4 * q4]);
+
+  // key tiles: the prefix's, then those covering the block's draft keys
+  const int n_pre = (Pb + 15) / 16;
+  const int t0 = rb * RB / p.G, t1 = (min(R, rb * RB + RB) - 1) / p.G;
+  const int slot_lo = (p.cross ? 0 : (t0 / p.L) * p.L) & ~15;
+  const int nt = n_pre + (min(p.T, (t1 / p.L + 1) * p.L) - slot_lo + 15) / 16;
+  const float* kc = p.k_cache + (size_t)bg * p.C * D;
+  const float* vc = p.v_cache + (size_t)bg * p.C * D;
+  const float* ks_ = p.k_slot + (size_t)bg * p.T * D;
+  const float* vs_ = p.v_slot + (size_t)bg * p.T * D;
+
+  f32x4 oacc[NR][NOB];
+  float m[NR], l[NR];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    m[r] = -INFINITY;
+    l[r] = 0.f;
+#pragma unroll
+    for (int ob = 0; ob < NOB; ++ob) oacc[r][ob] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+
+  f32x4 kf[NKS];
+  // K row n of tile i, clamped to the last valid key (its score is masked)
+  auto load_k = [&](int i) {
+    const bool pre = i < n_pre;
+    const int key0 = pre ? 16 * i : slot_lo + 16 * (i - n_pre);
+    const float* src = (pre ? kc : ks_) + (size_t)min(key0 + n, (pre ? Pb : p.T) - 1) * D + 4 * q4;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) kf[ks] = load_f32x4(src + 16 * ks);
+  };
+
+  if (wave < nt) load_k(wave);
+  for (int i = wave; i < nt; i += NW) {
+    const bool pre = i < n_pre;
+    const int key0 = pre ? 16 * i : slot_lo + 16 * (i - n_pre);
+    const int last = (pre ? Pb : p.T) - 1;
+    const float* vsrc = pre ? vc : vs_;
+    f32x4 vf[4][NC];  // V rows 4 * q4 + v, elements 64 * c + 4 * n + e
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        vf[v][c] = load_f32x4(vsrc + (size_t)min(key0 + 4 * q4 + v, last) * D + 64 * c + 4 * n);
+
+    f32x4 s[NR];  // scores of keys 4 * q4 + v
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      f32x4 s0{0.f, 0.f, 0.f, 0.f}, s1{0.f, 0.f, 0.f, 0.f};  // two chains
+      // query fragments come from LDS for each tile (in registers they would
+      // not leave room for the output and the key and value pieces in flight)
+      bf16x8 qf[NKS];
+      const uint32_t qa = q_addr + r * 16 * OSTR * 4;
+      qf[0] = lds_read_b128<0>(qa);
+      qf[1] = lds_read_b128<64>(qa);
+      qf[2] = lds_read_b128<128>(qa);
+      qf[3] = lds_read_b128<192>(qa);
+      if constexpr (NKS == 8) {
+        qf[4] = lds_read_b128<256>(qa);
+        qf[5] = lds_read_b128<320>(qa);
+        qf[6] = lds_read_b128<384>(qa);
+        qf[7] = lds_read_b128<448>(qa);
+      }
+      lds_wait<0>();
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks) lds_tie(qf[ks]);
+#pragma unroll
+      for (int ks = 0; ks < NKS; ks += 2) {
+        const f32x4 qa4 = __builtin_bit_cast(f32x4, qf[ks]), qb4 = __builtin_bit_cast(f32x4, qf[ks + 1]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          s0 = mfma16x16x4_f32(kf[ks][e], qa4[e], s0);
+          s1 = mfma16x16x4_f32(kf[ks + 1][e], qb4[e], s1);
+        }
+      }
+      s[r] = s0 + s1;
+    }
+    // the next tile's keys take the registers of this one's and arrive during
+    // the softmax and the PV products
+    __builtin_amdgcn_sched_barrier(0);
+    if (i + NW < nt) load_k(i + NW);
+    __builtin_amdgcn_sched_barrier(0);
+    const bool masked = !pre || key0 + 16 > Pb;
+    auto visible = [&](int r, int key) { return pre ? key < Pb : key >= vis_lo[r] && key < vis_hi[r]; };
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      if (masked) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (!visible(r, key0 + 4 * q4 + v)) s[r][v] = -INFINITY;
+      }
+      float mt = max3f(max3f(s[r][0], s[r][1], s[r][2]), s[r][3], s[r][3]);
+      mt = fmaxf(mt, __shfl_xor(mt, 16));
+      mt = fmaxf(mt, __shfl_xor(mt, 32));
+      const float m_new = fmaxf(m[r], mt);
+      if (__any(m_new > m[r])) {
+        const float c = m[r] == -INFINITY ? 0.f : expf(m[r] - m_new);
+        l[r] *= c;
+#pragma unroll
+        for (int ob = 0; ob < NOB; ++ob)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) oacc[r][ob][v] *= c;
+        m[r] = m_new;
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        s[r][v] = s[r][v] == -INFINITY ? 0.f : expf(s[r][v] - m_new);
+        l[r] += s[r][v];
+      }
+    }
+    // A value a row does not see must not reach it, and 0 * inf or 0 * NaN
+    // would: such tiles (masked, with a value that is not finite) are summed
+    // key by key over the visible keys only.
+    bool bad = false;
+    if (masked) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) bad = bad || !(fabsf(vf[v][c][e]) < INFINITY);
+      bad = __any(bad);
+    }
+    if (!bad) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+#pragma unroll
+          for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              oacc[r][4 * c + e] = mfma16x16x4_f32(vf[v][c][e], s[r][v], oacc[r][4 * c + e]);
+    } else {
+#pragma unroll
+      for (int r = 0; r < NR; ++r)
+#pragma unroll 1
+        for (int j = 0; j < 16; ++j) {
+          const float pj = __shfl(j & 2 ? (j & 1 ? s[r][3] : s[r][2]) : (j & 1 ? s[r][1] : s[r][0]), 16 * (j >> 2) + n);
+          if (!visible(r, key0 + j)) continue;
+          const float* vrow = vsrc + (size_t)min(key0 + j, last) * D + 16 * q4;
+#pragma unroll
+          for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              const f32x4 vv = load_f32x4(vrow + 64 * c + 4 * v);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) oacc[r][4 * c + e][v] = fmaf(pj, vv[e], oacc[r][4 * c + e][v]);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+  }
+
+  // ---- merge of the waves' partials, in wave order
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    l[r] += __shfl_xor(l[r], 16);
+    l[r] += __shfl_xor(l[r], 32);
+    const int lr = 16 * r + n;
+    if (q4 == 0) {
+      part_m[wave][lr] = m[r];
+      part_l[wave][lr] = l[r];
+    }
+    // oacc[4 * c + e][v] is element 64 * c + 16 * q4 + 4 * v + e of the row
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        *reinterpret_cast<f32x4*>(&part_o[wave][lr][64 * c + 16 * q4 + 4 * v]) =
+            f32x4{oacc[r][4 * c][v], oacc[r][4 * c + 1][v], oacc[r][4 * c + 2][v], oacc[r][4 * c + 3][v]};
+  }
+  __syncthreads();
+  for (int x = threadIdx.x; x < RB * (D / 4); x += NW * 64) {
+    const int lr = x / (D / 4), c = 4 * (x % (D / 4));
+    const int row = rb * RB + lr;
+    if (row >= R) break;
+    float mx = part_m[0][lr];
+#pragma unroll
+    for (int i = 1; i < NW; ++i) mx = fmaxf(mx, part_m[i][lr]);
+    float lt = 0.f;
+    f32x4 o{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+      const float pm = part_m[i][lr], pl = part_l[i][lr];
+      if (pm == -INFINITY && pl == 0.f) continue;  // a wave without a visible key of this row
+      const float sc = expf(pm - mx);
+      lt += sc * pl;
+      o += sc * *reinterpret_cast<const f32x4*>(&part_o[i][lr][c]);
+    }
+    const size_t grow = (size_t)bg * R + (size_t)(row % p.G) * p.T + row / p.G;
+    store_f32x4(p.out + grow * D + c, o / lt);
+    if (p.lse && c == 0) p.lse[grow] = mx + logf(lt);
+  }
 }
 
 // ------------------------------------------------------------------ launchers
@@ -584,12 +779,22 @@ hipError_t launch_slot_attn_bf16(const AttnParams& p, int head_dim, hipStream_t 
   return hipGetLastError();
 }
 
-hipError_t launch_slot_attn_f32(const AttnParams32& p, int head_dim, hipStream_t stream) {
-  const int grid = (p.rows_total + kAttnF32RowsPerBlock - 1) / kAttnF32RowsPerBlock;
+template <int NR>
+void launch_attn_f32_rows(const AttnParams32& p, int head_dim, int n_rb, hipStream_t stream) {
+  const dim3 grid(8 * ((p.B * p.Hkv * n_rb + 7) / 8)), block(kAttnF32Waves * 64);
   if (head_dim == 128) {
-    hipLaunchKernelGGL(slot_attn_f32_kernel<128>, dim3(grid), dim3(kAttnF32RowsPerBlock * 8), 0, stream, p);
+    slot_attn_f32_kernel<128, NR><<<grid, block, 0, stream>>>(p);
   } else {
-    hipLaunchKernelGGL(slot_attn_f32_kernel<64>, dim3(grid), dim3(kAttnF32RowsPerBlock * 4), 0, stream, p);
+    slot_attn_f32_kernel<64, NR><<<grid, block, 0, stream>>>(p);
+  }
+}
+
+hipError_t launch_slot_attn_f32(const AttnParams32& p, int head_dim, hipStream_t stream) {
+  const int R = p.G * p.T, rows = attn_f32_rows_per_block(p.B * (int64_t)p.Hkv, R, (int64_t)p.P + p.T);
+  if (rows == 32) {
+    launch_attn_f32_rows<2>(p, head_dim, (R + 31) / 32, stream);
+  } else {
+    launch_attn_f32_rows<1>(p, head_dim, (R + 15) / 16, stream);
   }
   return hipGetLastError();
 }
