@@ -143,6 +143,7 @@ AttnPlan plan_attn(const zarya_slot_attn_desc* d) {
 
 struct ConfPlan {
   int n_vg, n_rt;
+  int vg_split;  // workgroups per vocabulary group (1 except on the float32 path)
   size_t ws_bytes;
 };
 
@@ -169,6 +170,7 @@ zarya_status check_conf_desc(const zarya_conf_desc* d) {
 
 ConfPlan plan_conf(const zarya_conf_desc* d) {
   ConfPlan pl{};
+  pl.vg_split = 1;
   if (d->dtype == ZARYA_DTYPE_BF16) {
     const int br = conf_tile_rows(d->n_rows);
     pl.n_rt = (d->n_rows + br - 1) / br;
@@ -179,15 +181,22 @@ ConfPlan plan_conf(const zarya_conf_desc* d) {
   } else {
     pl.n_rt = 1;
     pl.n_vg = std::max(1, std::min(64, d->vocab / 2048));
+    // with few row tiles each group is shared by several workgroups, up to
+    // about one workgroup per compute unit and 128 ids each (a group per
+    // workgroup left three quarters of the units idle at 64 rows)
+    const int br = conf_f32_tile_rows(d->n_rows);
+    const int64_t items = (int64_t)pl.n_vg * ((d->n_rows + br - 1) / br);
+    const int tiles = (d->vocab + kConfF32MinIds - 1) / kConfF32MinIds;
+    pl.vg_split = (int)std::max<int64_t>(1, std::min<int64_t>(kConfTargetWGs / items, tiles / pl.n_vg));
   }
-  pl.ws_bytes = 3 * align256((size_t)pl.n_vg * d->n_rows * 4);
+  pl.ws_bytes = 3 * align256((size_t)pl.n_vg * pl.vg_split * d->n_rows * 4);
   return pl;
 }
 
 // Sampling keeps two more partial arrays (best perturbed score and its id).
 size_t sample_ws_bytes(const zarya_conf_desc* d) {
   const ConfPlan pl = plan_conf(d);
-  return pl.ws_bytes + 2 * align256((size_t)pl.n_vg * d->n_rows * 4);
+  return pl.ws_bytes + 2 * align256((size_t)pl.n_vg * pl.vg_split * d->n_rows * 4);
 }
 
 // Device address of `scratch` on the current device, looked up once per
@@ -221,7 +230,7 @@ zarya_status run_conf(const zarya_conf_desc* d, const zarya_sample_params* sp, c
                       float* sample_prob, void* workspace, hipStream_t stream) {
   const ConfPlan pl = plan_conf(d);
   (void)hipGetLastError();
-  const size_t part = align256((size_t)pl.n_vg * d->n_rows * 4);
+  const size_t part = align256((size_t)pl.n_vg * pl.vg_split * d->n_rows * 4);
   char* ws = static_cast<char*>(workspace);
   ConfParams p{};
   p.hidden = hidden;
@@ -230,6 +239,7 @@ zarya_status run_conf(const zarya_conf_desc* d, const zarya_sample_params* sp, c
   p.H = d->hidden;
   p.V = d->vocab;
   p.n_vg = pl.n_vg;
+  p.vg_split = pl.vg_split;
   p.n_rt = pl.n_rt;
   p.n_items = pl.n_vg * pl.n_rt;
   p.per_xcd = (p.n_items + 7) / 8;
@@ -261,7 +271,7 @@ zarya_status run_conf(const zarya_conf_desc* d, const zarya_sample_params* sp, c
   mp.part_m = p.part_m;
   mp.part_s = p.part_s;
   mp.part_idx = p.part_idx;
-  mp.n_vg = pl.n_vg;
+  mp.n_vg = pl.n_vg * pl.vg_split;
   mp.M = d->n_rows;
   mp.H = d->hidden;
   mp.V = d->vocab;

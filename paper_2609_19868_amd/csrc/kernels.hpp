@@ -55,6 +55,7 @@ struct ConfParams {
   const void* w_vocab;  // [V, H]
   int M, H, V;
   int n_vg;        // vocabulary groups (partials per row)
+  int vg_split;    // float32 path: workgroups (and partials) per vocabulary group
   int n_rt;        // row tiles (bf16 path)
   int per_xcd, n_items;
   float* part_m;   // [M, n_vg]
@@ -194,6 +195,11 @@ constexpr size_t kConfScratchBytes = (size_t)1 << 20;
 // no longer fit either way and non-temporal W costs traffic and 1% of time).
 constexpr size_t kConfXResidentBytes = (size_t)3 << 20;
 constexpr int conf_tile_rows(int n_rows) { return n_rows <= kConfSmallMaxRows ? kConfSmallBR : kConfBR; }
+
+// float32 path: tiles of 64 rows x 128 vocab ids, or of 32 rows x 256 ids where
+// that is all the rows (half of a 64-row tile would be padding).
+constexpr int kConfF32MinIds = 128;  // ids a workgroup gets at least
+constexpr int conf_f32_tile_rows(int n_rows) { return n_rows <= 32 ? 32 : 64; }
 
 hipError_t launch_slot_attn_bf16(const AttnParams& p, int head_dim, hipStream_t stream);
 hipError_t launch_slot_attn_f32(const AttnParams32& p, int head_dim, hipStream_t stream);

@@ -72,11 +72,10 @@ __device__ __forceinline__ int cswz(int r) {
 // row block jb; offsets c >= lim are past the vocabulary range.  The argmax
 // is searched only when the tile raises the running maximum; the lowest id at
 // the maximum wins (earlier tiles hold lower ids).  ARGMAX = false skips it.
-template <int JB, bool ARGMAX = true>
-__device__ __forceinline__ void fold_tile(const f32x16 (&acc)[4][JB], int lim, int id0, float (&m_run)[JB],
+template <int IB, int JB, bool ARGMAX = true>
+__device__ __forceinline__ void fold_tile(const f32x16 (&acc)[IB][JB], int lim, int id0, float (&m_run)[JB],
                                           float (&s_run)[JB], int (&i_run)[JB]) {
-  constexpr int IB = 4;
-  const bool full = lim >= 128;
+  const bool full = lim >= 32 * IB;
 #pragma unroll
   for (int jb = 0; jb < JB; ++jb) {
     float mt = -INFINITY;
@@ -90,7 +89,12 @@ __device__ __forceinline__ void fold_tile(const f32x16 (&acc)[4][JB], int lim, i
         for (int v = 3; v < 15; v += 2) t = max3f(t, x[v], x[v + 1]);
         mq[ib] = max3f(t, x[15], x[15]);
       }
-      mt = max3f(max3f(mq[0], mq[1], mq[2]), mq[3], mq[3]);
+      if constexpr (IB == 4) {
+        mt = max3f(max3f(mq[0], mq[1], mq[2]), mq[3], mq[3]);
+      } else {
+        static_assert(IB <= 2, "one, two or four vocab blocks");
+        mt = fmaxf(mq[0], mq[IB - 1]);
+      }
     } else {
 #pragma unroll
       for (int ib = 0; ib < IB; ++ib)
@@ -155,12 +159,12 @@ __device__ __forceinline__ void fold_tile(const f32x16 (&acc)[4][JB], int lim, i
 // the winner's logit.  The row blocks are the inner loop so that each range
 // test on the vocab offset serves all of them (hoisted across row blocks, the
 // tests' lane masks overflow the scalar registers).
-template <int JB>
-__device__ __forceinline__ void sample_fold(const f32x16 (&acc)[4][JB], int lim, int id0, int row,
+template <int IB, int JB>
+__device__ __forceinline__ void sample_fold(const f32x16 (&acc)[IB][JB], int lim, int id0, int row,
                                             const ConfParams& p, float (&g_best)[JB], int (&g_id)[JB]) {
-  const bool full = lim >= 128;
+  const bool full = lim >= 32 * IB;
 #pragma unroll
-  for (int ib = 0; ib < 4; ++ib) {
+  for (int ib = 0; ib < IB; ++ib) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int c0 = ib * 32 + 8 * q;  // offsets c0 .. c0+3 hold ids id0 + c0 .. + 3
@@ -193,15 +197,17 @@ __device__ __forceinline__ void sample_merge(float& g, int& gi, float g2, int gi
 
 // Combine the statistics of a workgroup's rows and write one partial per
 // (vocabulary group, row).  Lanes n and n+32 hold disjoint vocab ids of the
-// same row (merged by a shuffle); the waves of vocab halves 0 and 1 hold the
-// same rows (merged through `scratch`, 20 bytes per row).  With SAMPLE the
-// sampling candidates are combined and written the same way (and the argmax,
-// not tracked then, is not written).  Contains a
-// workgroup barrier; `scratch` must be free of pending reads.
-template <int JB, int BR, bool SAMPLE>
-__device__ __forceinline__ void store_partials(const ConfParams& p, int vg, int row0, int rbase, int wv, int hh, int n,
-                                               float (&m_run)[JB], float (&s_run)[JB], int (&i_run)[JB],
-                                               float (&g_best)[JB], int (&g_id)[JB], uint8_t* scratch) {
+// same row (merged by a shuffle); the VW waves of the vocab slices hold the
+// same rows (merged through `scratch`, 20 bytes per row and slice but one).
+// With SAMPLE the sampling candidates are combined and written the same way
+// (and the argmax, not tracked then, is not written).  `n_vg` is the number of
+// partials of a row.  Contains a workgroup barrier; `scratch` must be free of
+// pending reads.
+template <int JB, int BR, int VW, bool SAMPLE>
+__device__ __forceinline__ void store_partials(const ConfParams& p, int n_vg, int vg, int row0, int rbase, int wv,
+                                               int hh, int n, float (&m_run)[JB], float (&s_run)[JB],
+                                               int (&i_run)[JB], float (&g_best)[JB], int (&g_id)[JB],
+                                               uint8_t* scratch) {
 #pragma unroll
   for (int jb = 0; jb < JB; ++jb) {
     const float m2 = __shfl_xor(m_run[jb], 32);
@@ -214,15 +220,16 @@ __device__ __forceinline__ void store_partials(const ConfParams& p, int vg, int 
       sample_merge(g_best[jb], g_id[jb], g2, gi2);
     }
   }
+  constexpr int N = (VW - 1) * BR;
   float* xm = reinterpret_cast<float*>(scratch);
-  float* xs = xm + BR;
-  int* xi = reinterpret_cast<int*>(xs + BR);
-  float* xg = reinterpret_cast<float*>(xi + BR);
-  int* xgi = reinterpret_cast<int*>(xg + BR);
-  if (wv == 1 && hh == 0) {
+  float* xs = xm + N;
+  int* xi = reinterpret_cast<int*>(xs + N);
+  float* xg = reinterpret_cast<float*>(xi + N);
+  int* xgi = reinterpret_cast<int*>(xg + N);
+  if (wv > 0 && hh == 0) {
 #pragma unroll
     for (int jb = 0; jb < JB; ++jb) {
-      const int lr = rbase + jb * 32 + n;
+      const int lr = (wv - 1) * BR + rbase + jb * 32 + n;
       xm[lr] = m_run[jb];
       xs[lr] = s_run[jb];
       xi[lr] = i_run[jb];
@@ -237,17 +244,18 @@ __device__ __forceinline__ void store_partials(const ConfParams& p, int vg, int 
 #pragma unroll
     for (int jb = 0; jb < JB; ++jb) {
       const int lr = rbase + jb * 32 + n;
-      stat_merge(m_run[jb], s_run[jb], i_run[jb], xm[lr], xs[lr], xi[lr]);
+#pragma unroll
+      for (int v = 0; v < VW - 1; ++v) {
+        stat_merge(m_run[jb], s_run[jb], i_run[jb], xm[v * BR + lr], xs[v * BR + lr], xi[v * BR + lr]);
+        if constexpr (SAMPLE) sample_merge(g_best[jb], g_id[jb], xg[v * BR + lr], xgi[v * BR + lr]);
+      }
       const int row = row0 + lr;
-      const size_t o = (size_t)row * p.n_vg + vg;
+      const size_t o = (size_t)row * n_vg + vg;
       if (row < p.M) {
         p.part_m[o] = m_run[jb];
         p.part_s[o] = s_run[jb];
         p.part_idx[o] = i_run[jb];
-      }
-      if constexpr (SAMPLE) {
-        sample_merge(g_best[jb], g_id[jb], xg[lr], xgi[lr]);
-        if (row < p.M) {
+        if constexpr (SAMPLE) {
           p.part_g[o] = g_best[jb];
           p.part_gi[o] = g_id[jb];
         }
@@ -496,92 +504,199 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
     }
     if (cc.kq == nks - 1) {
       if (active) {
-        fold_tile<JB, !SAMPLE>(acc, v_hi - vbase - 4 * hh, vbase + 4 * hh, m_run, s_run, i_run);
+        fold_tile<IB, JB, !SAMPLE>(acc, v_hi - vbase - 4 * hh, vbase + 4 * hh, m_run, s_run, i_run);
         if constexpr (SAMPLE)
-          sample_fold<JB>(acc, v_hi - vbase - 4 * hh, vbase + 4 * hh, row0 + rbase + n, p, g_best, g_id);
+          sample_fold<IB, JB>(acc, v_hi - vbase - 4 * hh, vbase + 4 * hh, row0 + rbase + n, p, g_best, g_id);
       }
     }
     advance(cc, NSW);
     if (++sx_c == NSX) sx_c = 0;
   }
   block_barrier();  // every wave is done with the stage buffers (reused below)
-  store_partials<JB, BR, SAMPLE>(p, vg, row0, rbase, wv, hh, n, m_run, s_run, i_run, g_best, g_id, &lds_w[0][0]);
+  store_partials<JB, BR, 2, SAMPLE>(p, p.n_vg, vg, row0, rbase, wv, hh, n, m_run, s_run, i_run, g_best, g_id, &lds_w[0][0]);
 }
 
-// float32 path: one workgroup per (vocabulary group, row); plain FMA dot products.
-__global__ __launch_bounds__(256) void slot_conf_f32_kernel(ConfParams p) {
-  extern __shared__ float hs[];  // [H] hidden row, then reduction scratch
-  const int vg = blockIdx.x, row = blockIdx.y;
-  const int tid = threadIdx.x;
-  const float* X = static_cast<const float*>(p.hidden);
+// float32 path: the same transposed product and per-lane reduction with
+// v_mfma_f32_32x32x2_f32 (float32 operands and accumulators).  Eight waves own
+// a tile of BR rows x 128 (BR = 64) or 256 (BR = 32) vocab ids, one 32 x 32
+// block each.  A stage is 32 deep (128 bytes a row, the bf16 kernel's LDS
+// geometry): a lane's 16-byte piece of a row holds its operand of four MFMAs,
+// whose order in k is free as long as both operands follow it.  Operands go
+// through a ring of direct-load LDS stages; two waves per SIMD cover each
+// other's waits.
+// WIDE: rows of 16-byte multiples at 16-byte aligned addresses, loaded 16
+// bytes per lane; otherwise 4 bytes per lane, which any row length and
+// alignment allows (four times the load instructions, still few beside a
+// stage's 16 MFMAs of 64 cycles per wave).
+// 64 x 1024 against 151936 ids takes 219 us, 91 TFLOP/s (float32 matrix rate
+// 140, W stream alone 121 us); with one scalar dot product per thread, as it
+// was before, 7870 us.  Four waves with two blocks each, one per SIMD, took
+// 267 us: nothing covered their barriers and their accumulators moved between
+// the register files in every stage.
+template <int BR, bool WIDE, bool SAMPLE>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void slot_conf_f32_kernel(ConfParams p) {
+  constexpr int NW = 8, BK = 32;
+  constexpr int NS = BR == 64 ? 6 : 4;       // LDS stages
+  constexpr int RW = BR / 32, VW = NW / RW;  // waves over the rows and over the vocab ids
+  constexpr int BVF = 32 * VW;               // vocab ids per tile
+  constexpr int WTB = BVF * BK * 4, XTB = BR * BK * 4;
+  constexpr int CPW = WTB / 1024 / NW;       // 1 KB pieces (8 rows) of the W tile per wave and stage; one of the hidden tile
+  constexpr int NL = WIDE ? 1 : 4;           // load instructions per piece
+  constexpr int LPS = (CPW + 1) * NL;        // loads per wave and stage
+  static_assert((NS - 2) * LPS < 64 && NS * (WTB + XTB) <= 160 * 1024, "tile geometry");
+  __shared__ __attribute__((aligned(16))) uint8_t lds_w[NS][WTB];
+  __shared__ __attribute__((aligned(16))) uint8_t lds_x[NS][XTB];
+
+  const int n_vg = p.n_vg * p.vg_split, n_rt = (p.M + BR - 1) / BR;
+  const int item = xcd_work_index(blockIdx.x, gridDim.x >> 3, n_vg * n_rt);
+  if (item < 0) return;
+  const int rt = item % n_rt, vg = item / n_rt;
+  const int nblk = (p.V + 31) / 32;
+  const int v_lo = (int)((long long)vg * nblk / n_vg) * 32;
+  const int v_hi = min(p.V, (int)((long long)(vg + 1) * nblk / n_vg) * 32);
+  const int n_vt = (v_hi - v_lo + BVF - 1) / BVF;
+  const int row0 = rt * BR, H = p.H;
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 31, hh = lane >> 5;
+  const int wr = wave % RW, wv = wave / RW;
+  const int rbase = wr * 32;
   const float* W = static_cast<const float*>(p.w_vocab);
-  const size_t xrow = (size_t)conf_hidden_row(p.row_index, p.hidden_rows, row);
-  for (int k = tid; k < p.H; k += 256) hs[k] = X[xrow * p.H + k];
-  __syncthreads();
-  const int v_lo = (int)((long long)vg * p.V / p.n_vg);
-  const int v_hi = (int)((long long)(vg + 1) * p.V / p.n_vg);
-  float m = kNegBig, s = 0.f;
-  int idx = INT_MAX;
-  float g = -INFINITY;  // sampling candidate
-  int gi = INT_MAX;
-  for (int v = v_lo + tid; v < v_hi; v += 256) {
-    const float* wr = W + (size_t)v * p.H;
-    float z = 0.f;
-    for (int k = 0; k < p.H; ++k) z = fmaf(hs[k], wr[k], z);
-    if (p.part_g) {
-      const uint4 r = philox4x32_10_dev((uint32_t)v >> 2, (uint32_t)row, p.off_lo, p.off_hi, p.seed_lo, p.seed_hi);
-      const uint32_t words[4] = {r.x, r.y, r.z, r.w};
-      const float sc = fmaf(z, p.c2t, gumbel_log2(words[v & 3]));
-      if (sc > g) {
-        g = sc;
-        gi = v;
+  const float* X = static_cast<const float*>(p.hidden);
+
+  // W piece j of a wave holds rows 64 * j + 8 * wave .. + 7 of the tile, its
+  // hidden piece rows 8 * xw .. + 7 (with BR = 32 two waves load each hidden
+  // piece, the same bytes to the same place, so that every wave counts the
+  // same loads); load t fills 8 / NL of them.  The lane's row within the load,
+  // and the logical column that the swizzle of that row (of period 16) puts at
+  // the lane's place, the same for both operands:
+  const int xw = wave % (BR / 8);
+  const int nks = (H + BK - 1) / BK, n_st = n_vt * nks;
+  const int rows_tail = H - (nks - 1) * BK;  // columns of the last stage
+  auto lrow = [&](int t) { return 8 * wave + (WIDE ? lane / 8 : 2 * t + lane / 32); };
+  auto lcol = [&](int t) {
+    const int pc = WIDE ? lane % 8 : (lane % 32) / 4;
+    return 4 * (pc ^ cswz<64>(lrow(t))) + (WIDE ? 0 : lane % 4);
+  };
+  const float* xp[NL];  // hidden rows, clamped to valid ones (their results are not stored)
+#pragma unroll
+  for (int t = 0; t < NL; ++t)
+    xp[t] = X + (size_t)conf_hidden_row(p.row_index, p.hidden_rows, min(row0 + 8 * (xw - wave) + lrow(t), p.M - 1)) * H;
+
+  int st = 0, vt_l = 0, kq_l = 0, slot_l = 0;  // the next stage to load
+  auto issue = [&]() {
+    const int kk = kq_l * BK;
+    const bool tail = kq_l == nks - 1;  // columns past H are clamped here and zeroed in LDS before use
+#pragma unroll
+    for (int t = 0; t < NL; ++t) {
+      const int col = tail ? min(kk + lcol(t), H - (WIDE ? 4 : 1)) : kk + lcol(t);
+#pragma unroll
+      for (int j = 0; j < CPW; ++j) {
+        const int v = min(v_lo + vt_l * BVF + 64 * j + lrow(t), p.V - 1);
+        uint8_t* dst = &lds_w[slot_l][(8 * j + wave) * 1024 + t * 256];
+        const float* src = W + (size_t)v * H + col;
+        if constexpr (WIDE) {
+          dma16(src, dst);
+        } else {
+          dma4(src, dst);
+        }
+      }
+      uint8_t* dst = &lds_x[slot_l][xw * 1024 + t * 256];
+      if constexpr (WIDE) {
+        dma16(xp[t] + col, dst);
+      } else {
+        dma4(xp[t] + col, dst);
       }
     }
-    if (z > m) {
-      s = s * fast_exp2((m - z) * kLog2e) + 1.f;
-      m = z;
-      idx = v;
+    ++st;
+    if (++kq_l == nks) {
+      kq_l = 0;
+      ++vt_l;
+    }
+    if (++slot_l == NS) slot_l = 0;
+  };
+  auto zero_k_tail = [&](int slot) {  // this wave's own pieces, already landed
+#pragma unroll
+    for (int t = 0; t < NL; ++t) {
+      if (lcol(t) < rows_tail) continue;
+      const int off = t * 256 + lane * (WIDE ? 16 : 4);
+#pragma unroll
+      for (int j = 0; j < CPW + 1; ++j) {
+        uint8_t* dst = j < CPW ? &lds_w[slot][(8 * j + wave) * 1024 + off] : &lds_x[slot][xw * 1024 + off];
+        if constexpr (WIDE) {
+          *reinterpret_cast<uint4*>(dst) = make_uint4(0, 0, 0, 0);
+        } else {
+          *reinterpret_cast<uint32_t*>(dst) = 0;
+        }
+      }
+    }
+  };
+
+  // two accumulators take the even and the odd MFMAs: half the chain of
+  // dependent additions, in time and in rounding
+  f32x16 acc[1][1] = {{f32x16{}}}, acc2{};
+  float m_run[1] = {kNegBig}, s_run[1] = {0.f}, g_best[1] = {-INFINITY};
+  int i_run[1] = {INT_MAX}, g_id[1] = {INT_MAX};
+
+  for (int i = 0; i < NS - 1 && st < n_st; ++i) issue();
+  int slot = 0, kq = 0, vt = 0;
+  for (int i = 0; i < n_st; ++i) {
+    if (i + NS - 2 < n_st) {
+      wait_vmcnt<(NS - 2) * LPS>();  // only the loads of the NS - 2 next stages may still fly
     } else {
-      s += fast_exp2((z - m) * kLog2e);
+      wait_vmcnt<0>();
     }
-  }
-  float* rm = hs + p.H;
-  float* rs = rm + 256;
-  int* ri = reinterpret_cast<int*>(rs + 256);
-  float* rg = reinterpret_cast<float*>(ri + 256);
-  int* rgi = reinterpret_cast<int*>(rg + 256);
-  rm[tid] = m;
-  rs[tid] = s;
-  ri[tid] = idx;
-  rg[tid] = g;
-  rgi[tid] = gi;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (tid < off) {
-      float a = rm[tid], b = rs[tid];
-      int c = ri[tid];
-      stat_merge(a, b, c, rm[tid + off], rs[tid + off], ri[tid + off]);
-      rm[tid] = a;
-      rs[tid] = b;
-      ri[tid] = c;
-      float g1 = rg[tid];
-      int i1 = rgi[tid];
-      sample_merge(g1, i1, rg[tid + off], rgi[tid + off]);
-      rg[tid] = g1;
-      rgi[tid] = i1;
+    if (kq == nks - 1 && rows_tail < BK) zero_k_tail(slot);
+    block_barrier();
+    if (st < n_st) issue();  // into the buffers read in the previous iteration
+
+    const int vbase = v_lo + vt * BVF + wv * 32;
+    if (vbase < v_hi) {
+      const uint32_t wa = lds_addr(lds_w[slot]) + (wv * 32 + n) * 128;
+      const uint32_t xa = lds_addr(lds_x[slot]) + (rbase + n) * 128;
+      bf16x8 a[4], bx[4];
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        const uint32_t col = ((2 * ks + hh) ^ cswz<64>(n)) << 4;
+        a[ks] = lds_read_b128<0>(wa + col);
+        bx[ks] = lds_read_b128<0>(xa + col);
+      }
+      auto step = [&](int ks) {
+        lds_tie(a[ks]);
+        lds_tie(bx[ks]);
+        const f32x4 a4 = __builtin_bit_cast(f32x4, a[ks]), b4 = __builtin_bit_cast(f32x4, bx[ks]);
+        acc[0][0] = mfma32x32x2_f32(a4[0], b4[0], acc[0][0]);
+        acc2 = mfma32x32x2_f32(a4[1], b4[1], acc2);
+        acc[0][0] = mfma32x32x2_f32(a4[2], b4[2], acc[0][0]);
+        acc2 = mfma32x32x2_f32(a4[3], b4[3], acc2);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      lds_wait<6>();
+      step(0);
+      lds_wait<4>();
+      step(1);
+      lds_wait<2>();
+      step(2);
+      lds_wait<0>();
+      step(3);
+      if (kq == nks - 1) {
+        acc[0][0] += acc2;
+        fold_tile<1, 1, !SAMPLE>(acc, v_hi - vbase - 4 * hh, vbase + 4 * hh, m_run, s_run, i_run);
+        if constexpr (SAMPLE)
+          sample_fold<1, 1>(acc, v_hi - vbase - 4 * hh, vbase + 4 * hh, row0 + rbase + n, p, g_best, g_id);
+        acc[0][0] = acc2 = f32x16{};
+      }
     }
-    __syncthreads();
-  }
-  if (tid == 0) {
-    const size_t o = (size_t)row * p.n_vg + vg;
-    p.part_m[o] = rm[0];
-    p.part_s[o] = rs[0];
-    p.part_idx[o] = ri[0];
-    if (p.part_g) {
-      p.part_g[o] = rg[0];
-      p.part_gi[o] = rgi[0];
+    if (++kq == nks) {
+      kq = 0;
+      ++vt;
     }
+    if (++slot == NS) slot = 0;
   }
+  block_barrier();  // every wave is done with the stage buffers (reused below)
+  store_partials<1, BR, VW, SAMPLE>(p, n_vg, vg, row0, rbase, wv, hh, n, m_run, s_run, i_run, g_best, g_id,
+                                    &lds_w[0][0]);
 }
 
 // Logit of vocab id v for a row, hidden . w_vocab[v], as a float32 dot
@@ -696,9 +811,25 @@ hipError_t launch_slot_conf_bf16(const ConfParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
+template <int BR, bool WIDE>
+void launch_conf_f32_tile(const ConfParams& p, hipStream_t stream) {
+  const int n_items = p.n_vg * p.vg_split * ((p.M + BR - 1) / BR);
+  const dim3 grid(8 * ((n_items + 7) / 8)), block(512);
+  if (p.part_g) {
+    slot_conf_f32_kernel<BR, WIDE, true><<<grid, block, 0, stream>>>(p);
+  } else {
+    slot_conf_f32_kernel<BR, WIDE, false><<<grid, block, 0, stream>>>(p);
+  }
+}
+
 hipError_t launch_slot_conf_f32(const ConfParams& p, hipStream_t stream) {
-  const size_t shm = (size_t)p.H * 4 + 256 * 20;
-  hipLaunchKernelGGL(slot_conf_f32_kernel, dim3(p.n_vg, p.M), dim3(256), shm, stream, p);
+  // 16-byte loads where every row starts on a 16-byte boundary
+  const bool wide = p.H % 4 == 0 && (reinterpret_cast<uintptr_t>(p.hidden) | reinterpret_cast<uintptr_t>(p.w_vocab)) % 16 == 0;
+  if (conf_f32_tile_rows(p.M) == 32) {
+    wide ? launch_conf_f32_tile<32, true>(p, stream) : launch_conf_f32_tile<32, false>(p, stream);
+  } else {
+    wide ? launch_conf_f32_tile<64, true>(p, stream) : launch_conf_f32_tile<64, false>(p, stream);
+  }
   return hipGetLastError();
 }
 
