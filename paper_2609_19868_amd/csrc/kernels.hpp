@@ -182,6 +182,9 @@ constexpr int attn_f32_rows_per_block(int64_t groups, int64_t rows_per_group, in
 constexpr int kConfNW = 8, kConfBR = 256, kConfBK = 64, kConfNSW = 3, kConfNSX = 2;
 constexpr int kConfSmallNW = 4, kConfSmallBR = 64, kConfSmallMaxRows = 128;
 constexpr int kConfTargetWGs = 256;
+// Partials of one row at most, on either path (the merge holds them all in a wave).
+constexpr int kConfMaxGroups = 256;
+static_assert(kConfTargetWGs <= kConfMaxGroups, "groups per row");
 // Device scratch of zarya_slot_confidence_noalloc: room for the partials of
 // every bf16 call up to 65536 rows (row tiles x vocabulary groups <= 256, 12
 // bytes per row and group).

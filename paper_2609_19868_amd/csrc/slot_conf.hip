@@ -730,22 +730,42 @@ __device__ float row_logit(const ConfMergeParams& p, int hrow, int v, int lane) 
 // Per row (one wave): merge the vocabulary-group partials in a fixed order
 // and finish max_prob = 1 / sum exp(x - max), lse, the target probability
 // and, when sampling, the sampled id and its probability.
+// Bound by memory latency (a few KB per row): every partial of a row (at most
+// kConfMaxGroups) and the target's logit are requested before anything waits
+// (64 rows x 256 partials 8.0 -> 6.2 us; a single-sequence step 84.8 -> 84.2).
 __global__ __launch_bounds__(256) void slot_conf_merge_kernel(ConfMergeParams p) {
+  constexpr int NG = kConfMaxGroups / 64;  // partials per lane
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (row >= p.M) return;
-  // loads that do not depend on the partials go first, so that their latency
-  // overlaps the partials' (the target logit needs the target id)
   const int tgt = p.target_ids ? p.target_ids[row] : -1;
   const int hrow = conf_hidden_row(p.row_index, p.hidden_rows, row);
+  float pm[NG], ps[NG], pg[NG];
+  int pi[NG], pgi[NG];
+#pragma unroll
+  for (int j = 0; j < NG; ++j) {
+    // a row's partials are contiguous; lanes past the last one re-read it and drop it below
+    const size_t o = (size_t)row * p.n_vg + min(lane + 64 * j, p.n_vg - 1);
+    pm[j] = p.part_m[o];
+    ps[j] = p.part_s[o];
+    pi[j] = p.part_idx[o];
+    if (p.part_g) {
+      pg[j] = p.part_g[o];
+      pgi[j] = p.part_gi[o];
+    }
+  }
+  const bool tgt_in = tgt >= 0 && tgt < p.V;
+  const float zt = tgt_in ? row_logit(p, hrow, tgt, lane) : 0.f;
   float m = kNegBig, s = 0.f;
   int idx = INT_MAX;
   float sg = -INFINITY;
   int sgi = INT_MAX;
-  for (int g = lane; g < p.n_vg; g += 64) {
-    const size_t o = (size_t)row * p.n_vg + g;  // a row's partials are contiguous
-    stat_merge(m, s, idx, p.part_m[o], p.part_s[o], p.part_idx[o]);
-    if (p.part_g) sample_merge(sg, sgi, p.part_g[o], p.part_gi[o]);
+#pragma unroll
+  for (int j = 0; j < NG; ++j) {
+    if (lane + 64 * j < p.n_vg) {
+      stat_merge(m, s, idx, pm[j], ps[j], pi[j]);
+      if (p.part_g) sample_merge(sg, sgi, pg[j], pgi[j]);
+    }
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -762,15 +782,14 @@ __global__ __launch_bounds__(256) void slot_conf_merge_kernel(ConfMergeParams p)
   const float lse2 = m * kLog2e + __log2f(s);
   // A row whose logits include a NaN or an infinity has no softmax: its sum
   // is NaN (or 0 when every logit is -inf), so its log-sum-exp is not finite.
-  // Such a row reports id -1 and NaN probabilities, and no logit is recomputed
-  // for it (its ids are not meaningful).  Every lane holds the same merged
-  // statistics, so these conditions are uniform over the wave, as the dot
-  // products' shuffles need.
+  // Such a row reports id -1 and NaN probabilities, and its sample's logit is
+  // not recomputed (its ids are not meaningful).  Every lane holds the same
+  // merged statistics, so these conditions are uniform over the wave, as the
+  // dot products' shuffles need.
   const bool no_softmax = !(fabsf(lse2) < INFINITY);
-  const bool tgt_ok = tgt >= 0 && tgt < p.V && !no_softmax;
+  const bool tgt_ok = tgt_in && !no_softmax;
   const bool idx_ok = idx >= 0 && idx < p.V && !no_softmax;
   const bool sgi_ok = sgi >= 0 && sgi < p.V && !no_softmax;
-  const float zt = tgt_ok ? row_logit(p, hrow, tgt, lane) : 0.f;
   const float zs = p.part_g && sgi_ok ? row_logit(p, hrow, sgi, lane) : 0.f;
   if (lane != 0) return;
   // a row index outside the hidden rows was clamped for the loads: mark its results
