@@ -108,12 +108,14 @@ AttnPlan plan_attn(const zarya_slot_attn_desc* d) {
       ns = d->prefix_splits;
     } else {
       // aim for about one workgroup per compute unit (measured best on the
-      // 0.6B/1.7B/4B shapes), with at least two key tiles per split so the
-      // partial traffic stays small, and at most 8 splits: past that the
-      // merge of the partials costs more than the extra workgroups save
-      // (single-sequence batches: 8 splits 19.7 us, 16 splits 22.9 us)
+      // 0.6B/1.7B/4B shapes; where several splits reach it, not past it: a
+      // second workgroup on a few units doubles the longest).  A split costs
+      // its partials' round trip, so each keeps at least four key tiles, or
+      // two where that makes no more than eight splits.  One sequence, 8 x 128
+      // rows: 32 tiles 15.7 us at 8 splits, 16.7 at 16; 128 tiles 29.1 us at 8,
+      // 22.3 at 16, 20.1 at 32; 512 tiles 84.5, 50.2 and 37.3 us
       const int64_t base = (int64_t)d->batch * d->n_kv_heads * pl.n_rb;
-      int64_t want = (256 + base - 1) / base;
+      int64_t want = base <= 128 ? 256 / base : (256 + base - 1) / base;
       // long prefixes: two workgroups per compute unit when every split
       // still walks at least 64 key tiles, so that one workgroup's softmax
       // overlaps the other's MFMAs (4B shape, 256 tiles: 383 us with two
@@ -122,8 +124,8 @@ AttnPlan plan_attn(const zarya_slot_attn_desc* d) {
       // (256-row workgroups already hold two waves per SIMD and fit once per
       // compute unit)
       if (pl.rows_per_block == kAttnRowsPerBlock && pl.n_prefix_tiles >= 128 * want) want *= 2;
-      ns = (int)std::min<int64_t>(8, std::max<int64_t>(1, want));
-      ns = std::max(1, std::min(ns, pl.n_prefix_tiles / 2));
+      ns = (int)std::min<int64_t>(64, std::max<int64_t>(1, want));
+      ns = std::max(1, std::min(ns, std::max(std::min(8, pl.n_prefix_tiles / 2), pl.n_prefix_tiles / 4)));
     }
     ns = std::min(ns, pl.n_prefix_tiles);
     pl.tiles_per_split = (pl.n_prefix_tiles + ns - 1) / ns;
