@@ -26,19 +26,29 @@
 //    and a merge kernel combines them exactly.  With one split the kernel
 //    writes the final bf16 output itself.  The draft tokens' own keys are
 //    processed by the last split, with the mask applied per element.
+#include <type_traits>
+#include <utility>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
 namespace zarya {
 
-#ifndef ZARYA_ATTN_NS
-#define ZARYA_ATTN_NS 2  // LDS stages of the bf16 kernel (2 x 32 KB: two workgroups per CU)
-#endif
 #ifndef ZARYA_ATTN_WPE
 #define ZARYA_ATTN_WPE 2  // waves per SIMD the register budget is sized for
 #endif
 
 namespace {
+
+// f(std::integral_constant<int, 0>{}) ... f(std::integral_constant<int, N - 1>{})
+template <class F, int... I>
+__device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F&& f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for(std::make_integer_sequence<int, N>{}, f);
+}
 
 constexpr int KT = 64;          // keys per tile
 constexpr float kRescaleLog2 = 8.f;  // growth of a row maximum (log2 units) that forces a rescale
@@ -60,9 +70,10 @@ __host__ __device__ constexpr int swz(int kr) {
 
 }  // namespace
 
-// NS: LDS stages (prefetch distance NS - 1 tiles).  NWAVE: waves per
-// workgroup, 32 query rows each; every wave stages its share of each K/V tile.
-template <int D, int NS, int NWAVE>
+// NWAVE: waves per workgroup, 32 query rows each; every wave stages its share
+// of each K/V tile, one tile ahead (two LDS buffers of 32 KB at D = 128, which
+// leaves room for two workgroups per CU).
+template <int D, int NWAVE>
 __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(ZARYA_ATTN_WPE))) void slot_attn_bf16_kernel(AttnParams p) {
   constexpr int RB = NWAVE * 32;        // query rows per workgroup
   constexpr int ROWB = D * 2;           // bytes per key row
@@ -72,9 +83,8 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(ZARY
   constexpr int RPC = 1024 / ROWB;      // rows per 1 KB chunk
   constexpr int NDB = D / 32;           // 32-wide blocks of the head dim
   constexpr int NKS = D / 16;           // k-steps of the QK^T contraction
-  constexpr int LPT = 2 * CPW;          // direct loads per wave per tile
   static_assert(CPW * NWAVE * 1024 == TILEB, "tile must split into 1 KB chunks per wave");
-  __shared__ __attribute__((aligned(16))) uint8_t lds[NS][2][TILEB];
+  __shared__ __attribute__((aligned(16))) uint8_t lds[2][2][TILEB];
 
   int rb, split, bg;  // row block, prefix split, b * Hkv + g
   if (p.heavy_first) {
@@ -169,7 +179,7 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(ZARY
   const char* vc = reinterpret_cast<const char*>(p.v_cache + (size_t)bg * p.C * D);
   const char* ks_ = reinterpret_cast<const char*>(p.k_slot + (size_t)bg * p.T * D);
   const char* vs_ = reinterpret_cast<const char*>(p.v_slot + (size_t)bg * p.T * D);
-  auto issue = [&](int i, int buf) {
+  auto issue = [&](int i, int buf) __attribute__((always_inline)) {
     const char *kp, *vp;
     int key0, valid;
     if (i < n_pre) {
@@ -214,20 +224,24 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(ZARY
   const uint32_t lds0 = lds_addr(&lds[0][0][0]);
   // K fragment of k-step ks: row n, logical chunk 2*ks + hh, i.e. physical
   // chunk (2*ks) ^ (hh ^ swz(n)) (2*ks is even, hh the low bit)
-  const uint32_t k_row = n * ROWB;
+  const uint32_t k_row = lds0 + n * ROWB;
   const uint32_t k_cx = (uint32_t)((hh ^ swz<D>(n)) << 4);
-  auto k_col = [&](int ks) { return k_row + (k_cx ^ ((uint32_t)ks << 5)); };
+  uint32_t k_addr[NKS];
+#pragma unroll
+  for (int ks = 0; ks < NKS; ++ks) k_addr[ks] = k_row + (k_cx ^ ((uint32_t)ks << 5));
   const int q16 = lane >> 4, rr = lane & 15;
   const int vrow = 4 * hh + (rr >> 2);  // first key row of this lane's transposing reads (+16*st, +8)
   // Rows vrow + 16 * step and vrow + 8 + 16 * step: the swizzle repeats every
   // 16 rows and, for vrow < 8, swz(vrow + 8) = swz(vrow) ^ 1, which flips bit
   // 4 of the address (the chunk's low bit): the second half of a step is read
   // at (v_col ^ 16) + 8 rows.
-  uint32_t v_col[NDB];
+  uint32_t v_addr[NDB][2];  // first and second half-step
 #pragma unroll
   for (int db = 0; db < NDB; ++db) {
     const int d = db * 32 + (q16 & 1) * 16 + 4 * (rr & 3);
-    v_col[db] = vrow * ROWB + (((d >> 3) ^ swz<D>(vrow)) << 4) + (d & 7) * 2;
+    const uint32_t v_col = vrow * ROWB + (((d >> 3) ^ swz<D>(vrow)) << 4) + (d & 7) * 2;
+    v_addr[db][0] = lds0 + TILEB + v_col;
+    v_addr[db][1] = lds0 + TILEB + (v_col ^ 16u) + 8 * ROWB;
   }
   static_assert((swz<D>(8) ^ swz<D>(0)) == 1, "second V half-step addressing assumes swz(r + 8) = swz(r) ^ 1");
 
@@ -238,19 +252,19 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(ZARY
   // ---- S^T = K Q^T of tile i for two 32-key blocks; register v of block kb
   // holds key kb*32 + 8*(v/4) + 4*hh + v%4 of the tile.  K fragments are read
   // one k-step ahead of their MFMAs (deeper read-ahead measured no faster).
-  auto qk = [&](int i) {
-    const uint32_t kb_addr = lds0 + (i % NS) * (2 * TILEB);
+  auto qk = [&](auto buf) __attribute__((always_inline)) {
+    constexpr int KB = decltype(buf)::value * 2 * TILEB;
     sacc[0] = f32x16{};
     sacc[1] = f32x16{};
     bf16x8 kf[2][2];
-    kf[0][0] = lds_read_b128<0>(kb_addr + k_col(0));
-    kf[0][1] = lds_read_b128<32 * ROWB>(kb_addr + k_col(0));
+    kf[0][0] = lds_read_b128<KB>(k_addr[0]);
+    kf[0][1] = lds_read_b128<KB + 32 * ROWB>(k_addr[0]);
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) {
       const int sl = ks & 1;
       if (ks + 1 < NKS) {
-        kf[sl ^ 1][0] = lds_read_b128<0>(kb_addr + k_col(ks + 1));
-        kf[sl ^ 1][1] = lds_read_b128<32 * ROWB>(kb_addr + k_col(ks + 1));
+        kf[sl ^ 1][0] = lds_read_b128<KB>(k_addr[ks + 1]);
+        kf[sl ^ 1][1] = lds_read_b128<KB + 32 * ROWB>(k_addr[ks + 1]);
         lds_wait<2>();
       } else {
         lds_wait<0>();
@@ -262,18 +276,18 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(ZARY
     }
   };
 
-  // ---- V^T fragments of the first PV step of tile i
-  auto pv_start = [&](int i) {
-    const uint32_t vb_addr = lds0 + (i % NS) * (2 * TILEB) + TILEB;
+  // ---- V^T fragments of PV step `stp` of a tile
+  auto pv_read = [&](auto buf, auto stp) __attribute__((always_inline)) {
+    constexpr int OFF = decltype(buf)::value * 2 * TILEB + 16 * decltype(stp)::value * ROWB;
 #pragma unroll
     for (int db = 0; db < NDB; ++db) {
-      vf[0][db][0] = lds_read_tr16_b64<0>(vb_addr + v_col[db]);
-      vf[0][db][1] = lds_read_tr16_b64<8 * ROWB>(vb_addr + (v_col[db] ^ 16u));
+      vf[decltype(stp)::value & 1][db][0] = lds_read_tr16_b64<OFF>(v_addr[db][0]);
+      vf[decltype(stp)::value & 1][db][1] = lds_read_tr16_b64<OFF>(v_addr[db][1]);
     }
   };
 
   // ---- online softmax of tile i's scores; masks only on tiles that need them
-  auto softmax = [&](int i) {
+  auto softmax = [&](int i) __attribute__((always_inline)) {
     const bool is_slot = i >= n_pre;
     const int key0 = is_slot ? slot_lo + (i - n_pre) * KT : (pre_begin + i) * KT;
     const bool full = !is_slot && key0 + KT <= Pb;
@@ -341,62 +355,49 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(ZARY
     l_run += (ps[0] + ps[1]) + (ps[2] + ps[3]);
   };
 
-  // ---- O^T += V^T P^T of tile i (after pv_start(i)).  Step st covers keys
-  // 16*st + 4*hh + {0..3} (slots 0-3) and 16*st + 8 + 4*hh + {0..3} (slots
+  // ---- O^T += V^T P^T of tile i (after pv_read of step 0).  Step st covers
+  // keys 16*st + 4*hh + {0..3} (slots 0-3) and 16*st + 8 + 4*hh + {0..3} (slots
   // 4-7); V^T fragments are read one step ahead with the transposing LDS read.
-  auto pv_finish = [&](int i) {
-    const uint32_t vb_addr = lds0 + (i % NS) * (2 * TILEB) + TILEB;
-#pragma unroll
-    for (int stp = 0; stp < 4; ++stp) {
-      const int sl = stp & 1;
-      if (stp + 1 < 4) {
-#pragma unroll
-        for (int db = 0; db < NDB; ++db) {
-          vf[sl ^ 1][db][0] = lds_read_tr16_b64<0>(vb_addr + v_col[db] + 16 * (stp + 1) * ROWB);
-          vf[sl ^ 1][db][1] = lds_read_tr16_b64<8 * ROWB>(vb_addr + (v_col[db] ^ 16u) + 16 * (stp + 1) * ROWB);
-        }
+  auto pv = [&](auto buf) __attribute__((always_inline)) {
+    static_for<4>([&](auto stp) __attribute__((always_inline)) {
+      constexpr int st = decltype(stp)::value;
+      if constexpr (st + 1 < 4) {
+        pv_read(buf, std::integral_constant<int, st + 1>{});
         lds_wait<2 * NDB>();
       } else {
         lds_wait<0>();
       }
 #pragma unroll
       for (int db = 0; db < NDB; ++db) {
-        lds_tie(vf[sl][db][0]);
-        lds_tie(vf[sl][db][1]);
-        const uint2 l2 = __builtin_bit_cast(uint2, vf[sl][db][0]);
-        const uint2 h2 = __builtin_bit_cast(uint2, vf[sl][db][1]);
+        v4i16(&f)[2] = vf[st & 1][db];
+        lds_tie(f[0]);
+        lds_tie(f[1]);
+        const uint2 l2 = __builtin_bit_cast(uint2, f[0]);
+        const uint2 h2 = __builtin_bit_cast(uint2, f[1]);
         const bf16x8 a = __builtin_bit_cast(bf16x8, make_uint4(l2.x, l2.y, h2.x, h2.y));
-        oacc[db] = mfma32x32x16(a, pb[stp], oacc[db]);
+        oacc[db] = mfma32x32x16(a, pb[st], oacc[db]);
       }
-    }
+    });
   };
 
-  for (int st = 0; st < NS - 1 && st < nt; ++st) issue(st, st);
-  for (int i = 0; i < nt; ++i) {
-    const int ahead = min(nt - 1, i + NS - 2) - i;  // later tiles whose loads may still fly
-    if constexpr (NS >= 4) {
-      if (ahead >= 2) {
-        wait_vmcnt<2 * LPT>();
-      } else if (ahead == 1) {
-        wait_vmcnt<LPT>();
-      } else {
-        wait_vmcnt<0>();
-      }
-    } else if constexpr (NS == 3) {
-      if (ahead >= 1) {
-        wait_vmcnt<LPT>();
-      } else {
-        wait_vmcnt<0>();
-      }
-    } else {
-      wait_vmcnt<0>();
-    }
+  // The LDS buffer of a tile is a compile-time constant of its half of the
+  // loop, so that every fragment address is a register set up once plus an
+  // immediate offset (the 40 additions per tile it saves are a tenth of the
+  // vector instructions beside the MFMAs, and the two hardly overlap: the 4B
+  // shape 295 -> 282 us, the training layout 645 -> 626 us).
+  auto step = [&](int i, auto buf) __attribute__((always_inline)) {
+    wait_vmcnt<0>();
     block_barrier();
-    if (i + NS - 1 < nt) issue(i + NS - 1, (i + NS - 1) % NS);
-    qk(i);
-    pv_start(i);  // in flight during the softmax
+    if (i + 1 < nt) issue(i + 1, decltype(buf)::value ^ 1);
+    qk(buf);
+    pv_read(buf, std::integral_constant<int, 0>{});  // in flight during the softmax
     softmax(i);
-    pv_finish(i);
+    pv(buf);
+  };
+  if (nt > 0) issue(0, 0);
+  for (int i = 0; i < nt; i += 2) {
+    step(i, std::integral_constant<int, 0>{});
+    if (i + 1 < nt) step(i + 1, std::integral_constant<int, 1>{});
   }
 
   // ---- finalize: combine the two lane halves' partial sums
@@ -785,15 +786,15 @@ hipError_t launch_slot_attn_bf16(const AttnParams& p, int head_dim, hipStream_t 
   const bool wide = p.rows_per_block == kAttnWideRowsPerBlock;
   if (head_dim == 128) {
     if (wide) {
-      slot_attn_bf16_kernel<128, ZARYA_ATTN_NS, 8><<<dim3(grid), dim3(512), 0, stream>>>(p);
+      slot_attn_bf16_kernel<128, 8><<<dim3(grid), dim3(512), 0, stream>>>(p);
     } else {
-      slot_attn_bf16_kernel<128, ZARYA_ATTN_NS, 4><<<dim3(grid), dim3(256), 0, stream>>>(p);
+      slot_attn_bf16_kernel<128, 4><<<dim3(grid), dim3(256), 0, stream>>>(p);
     }
   } else {
     if (wide) {
-      slot_attn_bf16_kernel<64, ZARYA_ATTN_NS, 8><<<dim3(grid), dim3(512), 0, stream>>>(p);
+      slot_attn_bf16_kernel<64, 8><<<dim3(grid), dim3(512), 0, stream>>>(p);
     } else {
-      slot_attn_bf16_kernel<64, ZARYA_ATTN_NS, 4><<<dim3(grid), dim3(256), 0, stream>>>(p);
+      slot_attn_bf16_kernel<64, 4><<<dim3(grid), dim3(256), 0, stream>>>(p);
     }
   }
   hipError_t e = hipGetLastError();
