@@ -135,12 +135,16 @@ __device__ __forceinline__ void fold_tile(const f32x16 (&acc)[IB][JB], int lim, 
         __builtin_amdgcn_sched_barrier(0);  // keep the live ranges short
       }
     } else {
+      // a value of its own: the two branches' equal terms would be computed
+      // ahead of the branch, 16 * IB registers of them
+      float mn2p = mn2;
+      asm volatile("" : "+v"(mn2p));
 #pragma unroll
       for (int ib = 0; ib < IB; ++ib)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int c = ib * 32 + 8 * (v >> 2) + (v & 3);
-          const float pe = fast_exp2(fmaf(acc[ib][jb][v], kLog2e, -mn2));
+          const float pe = fast_exp2(fmaf(acc[ib][jb][v], kLog2e, -mn2p));
           e += c < lim ? pe : 0.f;
         }
     }
@@ -303,9 +307,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
   const int row0 = rt * BR;
   const int H = p.H;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // in a scalar register, as what follows from it
   const int n = lane & 31, hh = lane >> 5;
-  const int wv = wave & 1, wr = wave >> 1;  // vocab half, row slice
+  // vocab half, row slice: with eight waves each SIMD holds one wave of either
+  // half, so that a last tile that fills only the first half uses every SIMD
+  const int wv = wave / (NW / 2), wr = wave % (NW / 2);
   const int rbase = wr * WROWS;
 
   const uint16_t* W = static_cast<const uint16_t*>(p.w_vocab);
@@ -328,9 +335,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
   const int n_st = n_vt * nks;
   const bool k_ragged = (H % BK) != 0;
   const int lcol = lane % LPR, lrow = lane / LPR;
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);  // wave index in a scalar register
   static_assert((RPC * NW) % 16 == 0, "chunks must keep the swizzle phase");
-  const int l_row = RPC * wave_u + lrow;                        // row of this lane in chunk 0
+  const int l_row = RPC * wave + lrow;                        // row of this lane in chunk 0
   const int l_col = 8 * (lcol ^ cswz<BK>(l_row));               // its logical column, every chunk
   const uint32_t a_off = (uint32_t)(l_row * H + l_col) * 2u;    // in the W tile, chunk 0
   const uint32_t a_step = (uint32_t)(RPC * NW) * (uint32_t)H * 2u;  // bytes from chunk j to j+1
@@ -370,7 +376,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
       rsrc_w = buffer_rsrc(W + (size_t)vb * H, (uint32_t)((size_t)(min(p.V, vb + BV) - vb) * H * 2));
       cur_vt = vt;
     }
-    uint8_t* dst = &lds_w[cw.slot][wave_u * 1024];
+    uint8_t* dst = &lds_w[cw.slot][wave * 1024];
     const uint32_t off = (!k_ragged || kk + BK <= H) ? a_off : a_off + ragged_shift(kk);
 #pragma unroll
     for (int j = 0; j < CPA; ++j) dmab16<W_NT ? kLoadNonTemporal : 0>(rsrc_w, dst + NW * j * 1024, off + j * a_step, 2u * kk);
@@ -378,7 +384,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
   };
   auto issue_x = [&]() {  // the hidden tile of stage cx.st
     const int kk = cx.kq * BK;
-    uint8_t* dst = &lds_x[cx.slot][wave_u * 1024];
+    uint8_t* dst = &lds_x[cx.slot][wave * 1024];
     const int dk = (!k_ragged || kk + BK <= H) ? 0 : ragged_shift(kk);
 #pragma unroll
     for (int j = 0; j < CPB; ++j) dmab16(rsrc_x, dst + NW * j * 1024, b_off[j] + dk, 2u * kk);
@@ -409,13 +415,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
     g_id[j] = INT_MAX;
   }
 
-  // Load order: iteration i issues the hidden tile of stage i+NSX-1, then the
-  // W tile of stage i+NSW-1; the prologue issues what iterations before 0
-  // would have.  Loads complete in issue order, so when the hidden tile of
-  // stage i has landed so has its W tile, and with NSW = 3 only the W tile of
-  // stage i+1 (CPA loads) may still be in flight.  Waves with work issue the W
-  // tile after the MFMAs of the stage's first k-step, so that its address
-  // arithmetic runs while the matrix pipe is busy.
+  // Load order: stage j's entry (below) issues the hidden tile of stage
+  // j+NSX-1, then stage j the W tile of stage j+NSW-1; the prologue issues what
+  // stages before 0 would have.  Loads complete in issue order, so when the
+  // hidden tile of stage j has landed so has its W tile, and with NSW = 3 only
+  // the W tile of stage j+1 (CPA loads) may still be in flight.  Waves with
+  // work issue the W tile after the MFMAs of the stage's first k-step, so that
+  // its address arithmetic runs while the matrix pipe is busy.
   for (int j = -(NSW - 1); j < 0; ++j) {
     if (j + NSX - 1 >= 0 && cx.st < n_st) issue_x();
     if (cw.st < n_st) issue_w();
@@ -425,74 +431,76 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
   // compiler, which cannot see the LDS waits in inline assembly, re-waits for
   // them (lgkmcnt(0), also draining the fragment reads) inside the loop.
   __builtin_amdgcn_s_waitcnt(0xc07f);
-  Cursor cc{0, 0, 0, 0};  // the stage consumed by this iteration (slot: W ring)
+  Cursor cc{0, 0, 0, 0};  // the stage being consumed (slot: W ring)
   int sx_c = 0;           // its slot in the hidden ring
-  for (int i = 0; i < n_st; ++i) {
-    if (NSW == 3 && i + 1 < n_st) {
+
+  // Operand fragments are double-buffered across k-steps: the LDS reads of
+  // step ks+1 are issued before the MFMAs of step ks, which wait only for
+  // their own reads.  The swizzle of every row a lane reads depends on the
+  // lane alone, so one base address per step plus immediate offsets
+  // address all fragments of that step.
+  bf16x8 a[2][IB], bfr[2][JB];
+  auto frag_load = [&](int ks, int sl) __attribute__((always_inline)) {
+    const uint32_t off = n * (BK * 2) + (((2 * ks + hh) ^ cswz<BK>(n)) << 4);
+    const uint32_t pa = lds_addr(lds_w[0]) + cc.slot * ATB + wv * 128 * (BK * 2) + off;
+    const uint32_t pb = lds_addr(lds_x[0]) + sx_c * BTB + rbase * (BK * 2) + off;
+    a[sl][0] = lds_read_b128<0 * 32 * BK * 2>(pa);
+    a[sl][1] = lds_read_b128<1 * 32 * BK * 2>(pa);
+    a[sl][2] = lds_read_b128<2 * 32 * BK * 2>(pa);
+    a[sl][3] = lds_read_b128<3 * 32 * BK * 2>(pa);
+    bfr[sl][0] = lds_read_b128<0>(pb);
+    if constexpr (JB > 1) bfr[sl][1] = lds_read_b128<1 * 32 * BK * 2>(pb);
+    if constexpr (JB > 2) bfr[sl][2] = lds_read_b128<2 * 32 * BK * 2>(pb);
+    if constexpr (JB > 3) bfr[sl][3] = lds_read_b128<3 * 32 * BK * 2>(pb);
+  };
+  static_assert(IB == 4 && JB <= 4, "fragment loads are written out for IB = 4, JB <= 4");
+  static_assert(NKS % 2 == 0, "a stage's first fragments must land in the slot its last step does not use");
+  // Entry of the stage at `cc`: every wave's loads of it have landed and every
+  // wave has read the previous stage, whose hidden slot takes the next load.
+  auto enter_stage = [&]() __attribute__((always_inline)) {
+    if (NSW == 3 && cc.st + 1 < n_st) {
       wait_vmcnt<CPA>();
     } else {
       wait_vmcnt<0>();
     }
     if (k_ragged && cc.kq == nks - 1) zero_k_tail(cc);
     block_barrier();
-    // the buffers consumed in the previous iteration are free
     if (cx.st < n_st) issue_x();
-    const bool load_w = cw.st < n_st;
+    frag_load(0, 0);
+  };
 
-    const int vt = cc.vt;
-    // first vocab id of this wave's half, from the wave index in a scalar
-    // register so that `active` (and the stage cursors updated under it) stays
-    // wave-uniform for the compiler
-    const int vbase = v_lo + vt * BV + (wave_u & 1) * 128;
+  enter_stage();
+  for (int i = 0; i < n_st; ++i) {
+    const bool load_w = cw.st < n_st;
+    const int vbase = v_lo + cc.vt * BV + wv * 128;
     const bool active = vbase < v_hi;
-    const bool fresh = cc.kq == 0;
-    if (!active && load_w) issue_w();
+    const bool fresh = cc.kq == 0, last = cc.kq == nks - 1;
+    auto mfmas = [&](int sl) __attribute__((always_inline)) {
+#pragma unroll
+      for (int ib = 0; ib < IB; ++ib)
+#pragma unroll
+        for (int jb = 0; jb < JB; ++jb) acc[ib][jb] = mfma32x32x16(a[sl][ib], bfr[sl][jb], acc[ib][jb]);
+    };
+    auto tie = [&](int sl) __attribute__((always_inline)) {
+#pragma unroll
+      for (int ib = 0; ib < IB; ++ib) lds_tie(a[sl][ib]);
+#pragma unroll
+      for (int jb = 0; jb < JB; ++jb) lds_tie(bfr[sl][jb]);
+    };
     if (active) {
-      // Operand fragments are double-buffered across k-steps: the LDS reads of
-      // step ks+1 are issued before the MFMAs of step ks, which wait only for
-      // their own reads.  The swizzle of every row a lane reads depends on the
-      // lane alone, so one base address per step plus immediate offsets
-      // address all fragments of that step.
-      const uint32_t wsb = lds_addr(lds_w[cc.slot]), xsb = lds_addr(lds_x[sx_c]);
-      bf16x8 a[2][IB], bfr[2][JB];
-      auto frag_load = [&](int ks, int sl) {
-        const uint32_t col = ((2 * ks + hh) ^ cswz<BK>(n)) << 4;
-        const uint32_t pa = wsb + (wv * 128 + n) * (BK * 2) + col;
-        const uint32_t pb = xsb + (rbase + n) * (BK * 2) + col;
-        a[sl][0] = lds_read_b128<0 * 32 * BK * 2>(pa);
-        a[sl][1] = lds_read_b128<1 * 32 * BK * 2>(pa);
-        a[sl][2] = lds_read_b128<2 * 32 * BK * 2>(pa);
-        a[sl][3] = lds_read_b128<3 * 32 * BK * 2>(pa);
-        bfr[sl][0] = lds_read_b128<0>(pb);
-        if constexpr (JB > 1) bfr[sl][1] = lds_read_b128<1 * 32 * BK * 2>(pb);
-        if constexpr (JB > 2) bfr[sl][2] = lds_read_b128<2 * 32 * BK * 2>(pb);
-        if constexpr (JB > 3) bfr[sl][3] = lds_read_b128<3 * 32 * BK * 2>(pb);
-      };
-      static_assert(IB == 4 && JB <= 4, "fragment loads are written out for IB = 4, JB <= 4");
-      frag_load(0, 0);
 #pragma unroll
-      for (int ks = 0; ks < NKS; ++ks) {
+      for (int ks = 0; ks + 1 < NKS; ++ks) {
         const int sl = ks & 1;
-        if (ks + 1 < NKS) {
-          frag_load(ks + 1, sl ^ 1);
-          lds_wait<IB + JB>();  // this step's reads are done, the next step's may fly
-        } else {
-          lds_wait<0>();
-        }
-#pragma unroll
-        for (int ib = 0; ib < IB; ++ib) lds_tie(a[sl][ib]);
-#pragma unroll
-        for (int jb = 0; jb < JB; ++jb) lds_tie(bfr[sl][jb]);
+        frag_load(ks + 1, sl ^ 1);
+        lds_wait<IB + JB>();  // this step's reads are done, the next step's may fly
+        tie(sl);
         if (ks == 0 && fresh) {  // the tile's first k-step starts the accumulators from zero
 #pragma unroll
           for (int ib = 0; ib < IB; ++ib)
 #pragma unroll
             for (int jb = 0; jb < JB; ++jb) acc[ib][jb] = mfma32x32x16(a[sl][ib], bfr[sl][jb], f32x16{});
         } else {
-#pragma unroll
-          for (int ib = 0; ib < IB; ++ib)
-#pragma unroll
-            for (int jb = 0; jb < JB; ++jb) acc[ib][jb] = mfma32x32x16(a[sl][ib], bfr[sl][jb], acc[ib][jb]);
+          mfmas(sl);
         }
         // keep this step's MFMAs ahead of the next step's reads and waits
         __builtin_amdgcn_sched_barrier(0);
@@ -501,16 +509,32 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
           __builtin_amdgcn_sched_barrier(0);
         }
       }
+    } else if (load_w) {
+      issue_w();
     }
-    if (cc.kq == nks - 1) {
+    lds_wait<0>();
+    tie((NKS - 1) & 1);
+    advance(cc, NSW);
+    if (++sx_c == NSX) sx_c = 0;
+    const bool more = i + 1 < n_st;
+    // The next stage is entered before the last k-step's MFMAs, which cover its
+    // first fragment reads (48 KB that all eight waves ask for at once) -- but at
+    // the end of a vocab tile only after the fold, which needs their registers.
+    // 1024 x 2560 against 151936 ids 721 -> 704 us, 1024 x 1024 with draws 388 ->
+    // 380; the power limit takes part of what the shorter schedule gives (524 us
+    // on zeros).
+    if (!last) enter_stage();
+    __builtin_amdgcn_sched_barrier(0);
+    if (active) mfmas((NKS - 1) & 1);
+    __builtin_amdgcn_sched_barrier(0);
+    if (last) {
       if (active) {
         fold_tile<IB, JB, !SAMPLE>(acc, v_hi - vbase - 4 * hh, vbase + 4 * hh, m_run, s_run, i_run);
         if constexpr (SAMPLE)
           sample_fold<IB, JB>(acc, v_hi - vbase - 4 * hh, vbase + 4 * hh, row0 + rbase + n, p, g_best, g_id);
       }
+      if (more) enter_stage();
     }
-    advance(cc, NSW);
-    if (++sx_c == NSX) sx_c = 0;
   }
   block_barrier();  // every wave is done with the stage buffers (reused below)
   store_partials<JB, BR, 2, SAMPLE>(p, p.n_vg, vg, row0, rbase, wv, hh, n, m_run, s_run, i_run, g_best, g_id, &lds_w[0][0]);
