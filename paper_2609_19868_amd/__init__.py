@@ -75,23 +75,33 @@ _DT = {torch.bfloat16: DTYPE_BF16, torch.float32: DTYPE_F32}
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(dev):
-    """The current stream of `dev` (calls run inside `torch.cuda.device(dev)`,
-    so that the library launches on the tensors' device)."""
-    return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
+def _call(fn, dev, *args):
+    """fn(*args, current stream of dev) with dev current, since the library
+    launches on the current device; raises on an error status."""
+    if torch.cuda.current_device() == dev.index:
+        status = fn(*args, torch._C._cuda_getCurrentRawStream(dev.index))
+    else:
+        with torch.cuda.device(dev):
+            status = fn(*args, torch._C._cuda_getCurrentRawStream(dev.index))
+    if status != _lib.OK:
+        _lib.check(status)
 
 
 def _need(t, name, shape, dtype, device):
+    # Sixteen of these and three launches made up the 39 us of a selection,
+    # acceptance and append; with the plain comparisons below, raw pointers and
+    # no device switch where none is needed it takes 28 us (the kernels: 14).
+    if t.dtype is dtype and t.shape == shape and t.device == device and device.type == "cuda" and t.is_contiguous():
+        return
     if t.device.type != "cuda":
         raise ValueError(f"{name}: expected a cuda (HIP) device tensor, got one on {t.device}")
-    if t.device != device or t.dtype != dtype or tuple(t.shape) != tuple(shape) or not t.is_contiguous():
-        raise ValueError(
-            f"{name}: expected contiguous {dtype} {tuple(shape)} on {device}, "
-            f"got {t.dtype} {tuple(t.shape)} on {t.device} (contiguous={t.is_contiguous()})"
-        )
+    raise ValueError(
+        f"{name}: expected contiguous {dtype} {tuple(shape)} on {device}, "
+        f"got {t.dtype} {tuple(t.shape)} on {t.device} (contiguous={t.is_contiguous()})"
+    )
 
 
 def _need_opt(t, name, shape, dtype, device):
@@ -165,11 +175,9 @@ def slot_attn(q, k_cache, v_cache, k_slot, v_slot, n_slots, slot_len, pass_=PASS
     _need_workspace(workspace, ws_bytes, dev)
     if workspace is None and ws_bytes > 0:
         workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=dev)
-    with torch.cuda.device(dev):  # the library launches on the current device
-        _lib.check(_lib.lib().zarya_slot_attn(
-            ctypes.byref(desc), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(k_slot), _ptr(v_slot), _ptr(slot_pass),
-            _ptr(prefix_lens), _ptr(out), _ptr(lse), _ptr(workspace), 0 if workspace is None else workspace.numel(),
-            _stream(dev)))
+    _call(_lib.lib().zarya_slot_attn, dev, ctypes.byref(desc), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(k_slot),
+          _ptr(v_slot), _ptr(slot_pass), _ptr(prefix_lens), _ptr(out), _ptr(lse), _ptr(workspace),
+          0 if workspace is None else workspace.numel())
     return out, lse
 
 
@@ -204,11 +212,9 @@ def slot_confidence(hidden, w_vocab, target_ids=None, out=None, workspace=None):
     _need_workspace(workspace, ws_bytes, dev)
     if workspace is None:
         workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=dev)
-    with torch.cuda.device(dev):  # the library launches on the current device
-        _lib.check(_lib.lib().zarya_slot_confidence(
-            ctypes.byref(desc), _ptr(hidden), _ptr(w_vocab), _ptr(target_ids), _ptr(out["max_prob"]),
-            _ptr(out["argmax"]), _ptr(out.get("lse")), _ptr(out.get("target_prob")), _ptr(workspace),
-            workspace.numel(), _stream(dev)))
+    _call(_lib.lib().zarya_slot_confidence, dev, ctypes.byref(desc), _ptr(hidden), _ptr(w_vocab), _ptr(target_ids),
+          _ptr(out["max_prob"]), _ptr(out["argmax"]), _ptr(out.get("lse")), _ptr(out.get("target_prob")),
+          _ptr(workspace), workspace.numel())
     return out
 
 
@@ -245,11 +251,9 @@ def slot_sample(hidden, w_vocab, temperature, seed, offset=0, rows=None, out=Non
     _need_workspace(workspace, ws_bytes, dev)
     if workspace is None:
         workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=dev)
-    with torch.cuda.device(dev):  # the library launches on the current device
-        _lib.check(_lib.lib().zarya_slot_sample(
-            ctypes.byref(desc), ctypes.byref(params), _ptr(hidden), _ptr(rows), N, _ptr(w_vocab), _ptr(out["sample_id"]),
-            _ptr(out["sample_prob"]), _ptr(out.get("max_prob")), _ptr(out.get("lse")), _ptr(workspace),
-            workspace.numel(), _stream(dev)))
+    _call(_lib.lib().zarya_slot_sample, dev, ctypes.byref(desc), ctypes.byref(params), _ptr(hidden), _ptr(rows), N,
+          _ptr(w_vocab), _ptr(out["sample_id"]), _ptr(out["sample_prob"]), _ptr(out.get("max_prob")),
+          _ptr(out.get("lse")), _ptr(workspace), workspace.numel())
     return out
 
 
@@ -288,10 +292,8 @@ def mdm_reveal(mask, k, rule=REVEAL_CONFIDENCE, conf=None, seed=0, offset=0, sam
     order, n = out
     _need(order, "out[0] (order)", (B, N), torch.int32, dev)
     _need_opt(n, "out[1] (n_revealed)", (B,), torch.int32, dev)
-    with torch.cuda.device(dev):  # the library launches on the current device
-        _lib.check(_lib.lib().zarya_mdm_reveal(
-            B, N, _ptr(conf), _ptr(mask), _ptr(k), int(rule), int(seed) & (2**64 - 1), int(offset) & (2**64 - 1),
-            _ptr(sample_id), _ptr(tokens), _ptr(order), _ptr(n), _stream(dev)))
+    _call(_lib.lib().zarya_mdm_reveal, dev, B, N, _ptr(conf), _ptr(mask), _ptr(k), int(rule),
+          int(seed) & (2**64 - 1), int(offset) & (2**64 - 1), _ptr(sample_id), _ptr(tokens), _ptr(order), _ptr(n))
     return order, n
 
 
@@ -316,10 +318,8 @@ def select_slots(token_conf, slot_open=None, conf_rule=SLOT_CONF_FIRST_TOKEN, ru
     _need(slot_conf, "out[0] (slot_conf)", (B, S), torch.float32, dev)
     _need(selected, "out[1] (selected)", (B, S), torch.int32, dev)
     _need(n_selected, "out[2] (n_selected)", (B,), torch.int32, dev)
-    with torch.cuda.device(dev):  # the library launches on the current device
-        _lib.check(_lib.lib().zarya_select_slots(
-            B, S, L, _ptr(token_conf), _ptr(slot_open), int(conf_rule), int(rule), float(threshold), int(k),
-            _ptr(slot_conf), _ptr(selected), _ptr(n_selected), _stream(dev)))
+    _call(_lib.lib().zarya_select_slots, dev, B, S, L, _ptr(token_conf), _ptr(slot_open), int(conf_rule), int(rule),
+          float(threshold), int(k), _ptr(slot_conf), _ptr(selected), _ptr(n_selected))
     return slot_conf, selected, n_selected
 
 
@@ -345,10 +345,8 @@ def verify_accept(token_prob, selected, token_threshold=0.4, rule=ACCEPT_PREFIX,
     _need(accepted, "out[0] (accepted)", (B, S, L), torch.uint8, dev)
     _need(n_accepted, "out[1] (n_accepted)", (B, S), torch.int32, dev)
     _need_opt(n_total, "out[2] (n_total)", (B,), torch.int32, dev)
-    with torch.cuda.device(dev):  # the library launches on the current device
-        _lib.check(_lib.lib().zarya_verify_accept(
-            B, S, L, _ptr(token_prob), _ptr(selected), float(token_threshold), int(rule), _ptr(accepted),
-            _ptr(n_accepted), _ptr(n_total), _stream(dev)))
+    _call(_lib.lib().zarya_verify_accept, dev, B, S, L, _ptr(token_prob), _ptr(selected), float(token_threshold),
+          int(rule), _ptr(accepted), _ptr(n_accepted), _ptr(n_total))
     return accepted, n_accepted, n_total
 
 
@@ -371,8 +369,6 @@ def kv_append(k_cache, v_cache, prefix_lens, k_slot, v_slot, accepted, order):
     _need(prefix_lens, "prefix_lens", (B,), torch.int32, dev)
     desc = _lib.KvAppendDesc(batch=B, n_kv_heads=Hkv, head_dim=D, kv_capacity=C, n_slots=S, slot_len=L,
                              dtype=_DT[dt])
-    with torch.cuda.device(dev):  # the library launches on the current device
-        _lib.check(_lib.lib().zarya_kv_append(
-            ctypes.byref(desc), _ptr(k_slot), _ptr(v_slot), _ptr(accepted), _ptr(order), _ptr(prefix_lens),
-            _ptr(k_cache), _ptr(v_cache), _stream(dev)))
+    _call(_lib.lib().zarya_kv_append, dev, ctypes.byref(desc), _ptr(k_slot), _ptr(v_slot), _ptr(accepted),
+          _ptr(order), _ptr(prefix_lens), _ptr(k_cache), _ptr(v_cache))
     return k_cache, v_cache, prefix_lens
