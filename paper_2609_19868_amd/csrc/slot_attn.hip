@@ -385,10 +385,14 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(ZARY
   // immediate offset (the 40 additions per tile it saves are a tenth of the
   // vector instructions beside the MFMAs, and the two hardly overlap: the 4B
   // shape 295 -> 282 us, the training layout 645 -> 626 us).
+  // a wave of padding rows only helps to load the tiles (520 rows a group in
+  // blocks of 128, Mode A: the step 211 -> 207 us)
+  const bool live = rb * RB + wave_u * 32 < p.R;
   auto step = [&](int i, auto buf) __attribute__((always_inline)) {
     wait_vmcnt<0>();
     block_barrier();
     if (i + 1 < nt) issue(i + 1, decltype(buf)::value ^ 1);
+    if (!live) return;
     qk(buf);
     pv_read(buf, std::integral_constant<int, 0>{});  // in flight during the softmax
     softmax(i);
