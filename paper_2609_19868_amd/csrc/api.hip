@@ -331,7 +331,8 @@ zarya_status zarya_slot_attn_plan(const zarya_slot_attn_desc* desc, zarya_slot_a
     const int rows = attn_f32_rows_per_block(groups, pl.R, (int64_t)desc->prefix_len + pl.T);
     info->prefix_splits = 1;
     info->rows_per_workgroup = rows;
-    info->workgroups = (int32_t)(groups * ((pl.R + rows - 1) / rows));
+    const int64_t blocks = groups * ((pl.R + rows - 1) / rows);
+    info->workgroups = (int32_t)(blocks * attn_f32_row_parts(desc->head_dim, rows, blocks));
     info->kernels = 1;
     return ZARYA_OK;
   }

@@ -171,6 +171,13 @@ constexpr int kAttnWideRowsPerBlock = 256;  // eight waves: every K/V tile stage
 constexpr int attn_f32_rows_per_block(int64_t groups, int64_t rows_per_group, int64_t keys) {
   return groups * ((rows_per_group + 31) / 32) < 256 && keys > 16 * kAttnF32Waves ? 16 : 32;
 }
+// Workgroups per row block.  With 16 rows and at most half a workgroup per
+// compute unit two share a block: each computes all of the scores and half of
+// the value products, three quarters of the work on twice the units (D = 128;
+// at D = 64 half a row is less than the lanes' 16-byte pieces).
+constexpr int attn_f32_row_parts(int head_dim, int rows_per_block, int64_t blocks) {
+  return head_dim == 128 && rows_per_block == 16 && blocks <= 128 ? 2 : 1;
+}
 // Tile configuration of the bf16 LM-head reduction (measured on MI355X over
 // the 0.6B/1.7B/4B shapes): 8 waves over a 256 x 256 tile, 64-deep stages,
 // three W and two hidden LDS buffers (160 KB), one workgroup per compute

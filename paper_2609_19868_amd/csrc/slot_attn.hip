@@ -529,27 +529,34 @@ __global__ __launch_bounds__(256) void slot_attn_merge_kernel(const float* __res
 // the rows of a workgroup share each key through its waves' registers, and a
 // group's workgroups meet in one XCD's L2.
 //
-// Bound by the float32 matrix rate of the compute units that have rows: B = 2,
-// 16/8 heads, D = 128, 1000 + 64 keys, 64 tokens (128 workgroups of 16 rows)
-// takes 33 us, 32 TFLOP/s; one key at a time with a shuffled dot product per
-// row, as it was before, took 771 us.
-template <int D, int NR>
+// Bound by the float32 matrix rate of the compute units that have rows, and
+// the chain of a wave's tiles.  DS = 2: two workgroups take a row block, each
+// the whole scores and half of the output row (no exchange between them), for
+// launches that would leave half of the units idle.  B = 2, 16/8 heads, D = 128,
+// 1000 + 64 keys, 64 tokens (128 row blocks) takes 25.5 us, 42 TFLOP/s, and 32.7
+// with one workgroup a block; one key at a time with a shuffled dot product per
+// row, as it was at first, took 771 us.  Keys and values requested a whole tile
+// ahead (182 registers) took 26.7.
+template <int D, int NR, int DS>
 __global__ __launch_bounds__(kAttnF32Waves * 64) __attribute__((amdgpu_waves_per_eu(2))) void slot_attn_f32_kernel(
     AttnParams32 p) {
   constexpr int NW = kAttnF32Waves;
   constexpr int RB = 16 * NR;   // query rows per workgroup
   constexpr int NKS = D / 16;   // 16-byte pieces of a K row per lane
-  constexpr int NC = D / 64;    // 16-byte pieces of a V row per lane
-  constexpr int NOB = D / 16;   // 16-wide blocks of the output: block 4 * c + e holds d = 64 * c + 4 * i + e
-  constexpr int OSTR = D + 4;   // row stride of the partial outputs in LDS
+  constexpr int DO = D / DS;    // elements of the output row taken by this workgroup
+  constexpr int NC = DO / 64;   // 16-byte pieces of a V row per lane
+  constexpr int NOB = DO / 16;  // 16-wide blocks of the output: block 4 * c + e holds d = 64 * c + 4 * i + e
+  constexpr int OSTR = DO + 4;  // row stride of the partial outputs in LDS
+  constexpr int QSTR = D + 4;   // and of the queries
   __shared__ __attribute__((aligned(16))) float part_o[NW][RB][OSTR];
-  __shared__ __attribute__((aligned(16))) float qs[RB][OSTR];  // scaled queries; the padding spreads the rows over the banks
+  __shared__ __attribute__((aligned(16))) float qs[RB][QSTR];  // scaled queries; the padding spreads the rows over the banks
   __shared__ float part_m[NW][RB], part_l[NW][RB];
 
   const int n_rb = (p.G * p.T + RB - 1) / RB;
-  const int w = xcd_work_index(blockIdx.x, gridDim.x >> 3, p.B * p.Hkv * n_rb);
+  const int w = xcd_work_index(blockIdx.x, gridDim.x >> 3, p.B * p.Hkv * n_rb * DS);
   if (w < 0) return;
-  const int rb = w % n_rb, bg = w / n_rb;
+  const int d0 = (w % DS) * DO;  // first element taken
+  const int rb = w / DS % n_rb, bg = w / (DS * n_rb);
   const int b = bg / p.Hkv;
   const int R = p.G * p.T;
   const int lane = threadIdx.x & 63;
@@ -583,9 +590,9 @@ __global__ __launch_bounds__(kAttnF32Waves * 64) __attribute__((amdgpu_waves_per
   const int slot_lo = (p.cross ? 0 : (t0 / p.L) * p.L) & ~15;
   const int nt = n_pre + (min(p.T, (t1 / p.L + 1) * p.L) - slot_lo + 15) / 16;
   const float* kc = p.k_cache + (size_t)bg * p.C * D;
-  const float* vc = p.v_cache + (size_t)bg * p.C * D;
+  const float* vc = p.v_cache + (size_t)bg * p.C * D + d0;
   const float* ks_ = p.k_slot + (size_t)bg * p.T * D;
-  const float* vs_ = p.v_slot + (size_t)bg * p.T * D;
+  const float* vs_ = p.v_slot + (size_t)bg * p.T * D + d0;
 
   f32x4 oacc[NR][NOB];
   float m[NR], l[NR];
@@ -627,7 +634,7 @@ __global__ __launch_bounds__(kAttnF32Waves * 64) __attribute__((amdgpu_waves_per
       // query fragments come from LDS for each tile (in registers they would
       // not leave room for the output and the key and value pieces in flight)
       bf16x8 qf[NKS];
-      const uint32_t qa = q_addr + r * 16 * OSTR * 4;
+      const uint32_t qa = q_addr + r * 16 * QSTR * 4;
       qf[0] = lds_read_b128<0>(qa);
       qf[1] = lds_read_b128<64>(qa);
       qf[2] = lds_read_b128<128>(qa);
@@ -748,8 +755,8 @@ __global__ __launch_bounds__(kAttnF32Waves * 64) __attribute__((amdgpu_waves_per
             f32x4{oacc[r][4 * c][v], oacc[r][4 * c + 1][v], oacc[r][4 * c + 2][v], oacc[r][4 * c + 3][v]};
   }
   __syncthreads();
-  for (int x = threadIdx.x; x < RB * (D / 4); x += NW * 64) {
-    const int lr = x / (D / 4), c = 4 * (x % (D / 4));
+  for (int x = threadIdx.x; x < RB * (DO / 4); x += NW * 64) {
+    const int lr = x / (DO / 4), c = 4 * (x % (DO / 4));
     const int row = rb * RB + lr;
     if (row >= R) break;
     float mx = part_m[0][lr];
@@ -766,8 +773,8 @@ __global__ __launch_bounds__(kAttnF32Waves * 64) __attribute__((amdgpu_waves_per
       o += sc * *reinterpret_cast<const f32x4*>(&part_o[i][lr][c]);
     }
     const size_t grow = (size_t)bg * R + (size_t)(row % p.G) * p.T + row / p.G;
-    store_f32x4(p.out + grow * D + c, o / lt);
-    if (p.lse && c == 0) p.lse[grow] = mx + logf(lt);
+    store_f32x4(p.out + grow * D + d0 + c, o / lt);
+    if (p.lse && d0 + c == 0) p.lse[grow] = mx + logf(lt);
   }
 }
 
@@ -811,13 +818,20 @@ hipError_t launch_slot_attn_bf16(const AttnParams& p, int head_dim, hipStream_t 
   return hipGetLastError();
 }
 
+template <int D, int NR, int DS>
+void launch_attn_f32_as(const AttnParams32& p, int blocks, hipStream_t stream) {
+  slot_attn_f32_kernel<D, NR, DS><<<dim3(8 * ((DS * blocks + 7) / 8)), dim3(kAttnF32Waves * 64), 0, stream>>>(p);
+}
+
 template <int NR>
 void launch_attn_f32_rows(const AttnParams32& p, int head_dim, int n_rb, hipStream_t stream) {
-  const dim3 grid(8 * ((p.B * p.Hkv * n_rb + 7) / 8)), block(kAttnF32Waves * 64);
-  if (head_dim == 128) {
-    slot_attn_f32_kernel<128, NR><<<grid, block, 0, stream>>>(p);
+  const int blocks = p.B * p.Hkv * n_rb;
+  if (head_dim == 64) {
+    launch_attn_f32_as<64, NR, 1>(p, blocks, stream);
+  } else if (NR == 1 && attn_f32_row_parts(head_dim, 16, blocks) == 2) {
+    launch_attn_f32_as<128, 1, 2>(p, blocks, stream);
   } else {
-    slot_attn_f32_kernel<64, NR><<<grid, block, 0, stream>>>(p);
+    launch_attn_f32_as<128, NR, 1>(p, blocks, stream);
   }
 }
 

@@ -52,6 +52,24 @@ def test_f32_tiles(name, over, cross):
         assert check_attn(to_f64(out), to_f64(lse), O, L, "f32", f"{name} cross={cross}") <= 1e-5
 
 
+@pytest.mark.parametrize("batch", [6, 7], ids=["two_workgroups_a_block", "one"])
+def test_f32_around_the_shared_block_limit(batch):
+    """Five blocks of 16 rows per KV head (75 rows, the last block partly filled):
+    120 blocks are shared by two workgroups each, 140 are not."""
+    dev = require_gpu()
+    wl = W.WORKLOADS["qwen0.6b"].replace(batch=batch, n_q_heads=12, n_kv_heads=4, prefix_len=130, n_slots=5, slot_len=5,
+                                         dtype="f32", hidden=0, vocab=0, seed=95)
+    xd, xf = attn_inputs_dev(wl, dev)
+    plan = Z._lib.slot_attn_plan(Z.slot_attn_desc(xd["q"], xd["k_cache"], xd["k_slot"], 5, 5, prefix_len=130))
+    assert plan["rows_per_workgroup"] == 16 and plan["workgroups"] == {6: 240, 7: 140}[batch]
+    say(f"slot_attn f32 B={batch}")
+    out, lse = Z.slot_attn(xd["q"], xd["k_cache"], xd["v_cache"], xd["k_slot"], xd["v_slot"], 5, 5, prefix_len=130)
+    torch.cuda.synchronize()
+    O, L = oracle.slot_attention(xf["q"], xf["k_cache"], xf["v_cache"], xf["k_slot"], xf["v_slot"], 130, 5, 5, wl.scale,
+                                 oracle.PASS_DIFFUSION)
+    assert check_attn(to_f64(out), to_f64(lse), O, L, "f32", f"B={batch}") <= 1e-5
+
+
 @pytest.mark.parametrize("head_dim", [64, 128])
 @pytest.mark.parametrize("prefix_len", [20, 200], ids=["rows32", "rows16"])
 def test_f32_values_a_row_does_not_see_do_not_reach_it(head_dim, prefix_len):
