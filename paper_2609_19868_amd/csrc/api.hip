@@ -255,7 +255,11 @@ zarya_status run_conf(const zarya_conf_desc* d, const zarya_sample_params* sp, c
     // per_xcd items, row tile fastest) and the hidden rows they re-read
     const int64_t br = conf_tile_rows(d->n_rows);
     const int64_t rows_on_xcd = std::min<int64_t>(d->n_rows, std::min(pl.n_rt, p.per_xcd) * br);
-    p.w_stream = (size_t)rows_on_xcd * d->hidden * 2 <= kConfXResidentBytes ? 1 : 0;
+    // Where W's rows do not start on 128-byte lines, neighbouring stages share a
+    // line per row, which must stay in L2 between them (25 x 2184: 215 us
+    // non-temporal, 168 plain; 25 x 2560: 153 and 172)
+    const bool whole_lines = d->hidden % 64 == 0 && reinterpret_cast<uintptr_t>(w_vocab) % 128 == 0;
+    p.w_stream = whole_lines && (size_t)rows_on_xcd * d->hidden * 2 <= kConfXResidentBytes ? 1 : 0;
   }
   if (sp) {
     p.part_g = reinterpret_cast<float*>(ws + 3 * part);
