@@ -522,8 +522,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
     // the end of a vocab tile only after the fold, which needs their registers.
     // 1024 x 2560 against 151936 ids 721 -> 704 us, 1024 x 1024 with draws 388 ->
     // 380; the power limit takes part of what the shorter schedule gives (524 us
-    // on zeros).
-    if (!last) enter_stage();
+    // on zeros).  The few-row tile waits for the W stream, to which entering
+    // early leaves less time: 112 x 2048 163.6 us late, 165.4 early.
+    constexpr bool early = NW == 8;
+    if (early && !last) enter_stage();
     __builtin_amdgcn_sched_barrier(0);
     if (active) mfmas((NKS - 1) & 1);
     __builtin_amdgcn_sched_barrier(0);
@@ -533,8 +535,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
         if constexpr (SAMPLE)
           sample_fold<IB, JB>(acc, v_hi - vbase - 4 * hh, vbase + 4 * hh, row0 + rbase + n, p, g_best, g_id);
       }
-      if (more) enter_stage();
     }
+    if ((!early || last) && more) enter_stage();
   }
   block_barrier();  // every wave is done with the stage buffers (reused below)
   store_partials<JB, BR, 2, SAMPLE>(p, p.n_vg, vg, row0, rbase, wv, hh, n, m_run, s_run, i_run, g_best, g_id, &lds_w[0][0]);
