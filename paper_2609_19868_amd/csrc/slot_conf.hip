@@ -22,6 +22,8 @@
 // W tile is fetched from HBM once and reused from that XCD's L2.
 #include <limits.h>
 
+#include <type_traits>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -554,7 +556,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
 // bytes per lane; otherwise 4 bytes per lane, which any row length and
 // alignment allows (four times the load instructions, still few beside a
 // stage's 16 MFMAs of 64 cycles per wave).
-// 64 x 1024 against 151936 ids takes 219 us, 91 TFLOP/s (float32 matrix rate
+// 64 x 1024 against 151936 ids takes 214 us, 93 TFLOP/s (float32 matrix rate
 // 140, W stream alone 121 us); with one scalar dot product per thread, as it
 // was before, 7870 us.  Four waves with two blocks each, one per SIMD, took
 // 267 us: nothing covered their barriers and their accumulators moved between
@@ -611,7 +613,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void s
     xp[t] = X + (size_t)conf_hidden_row(p.row_index, p.hidden_rows, min(row0 + 8 * (xw - wave) + lrow(t), p.M - 1)) * H;
 
   int st = 0, vt_l = 0, kq_l = 0, slot_l = 0;  // the next stage to load
-  auto issue = [&]() {
+  auto issue = [&]() __attribute__((always_inline)) {
     const int kk = kq_l * BK;
     const bool tail = kq_l == nks - 1;  // columns past H are clamped here and zeroed in LDS before use
 #pragma unroll
@@ -642,7 +644,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void s
     }
     if (++slot_l == NS) slot_l = 0;
   };
-  auto zero_k_tail = [&](int slot) {  // this wave's own pieces, already landed
+  auto zero_k_tail = [&](int slot) __attribute__((always_inline)) {  // this wave's own pieces, already landed
 #pragma unroll
     for (int t = 0; t < NL; ++t) {
       if (lcol(t) < rows_tail) continue;
@@ -665,47 +667,77 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void s
   float m_run[1] = {kNegBig}, s_run[1] = {0.f}, g_best[1] = {-INFINITY};
   int i_run[1] = {INT_MAX}, g_id[1] = {INT_MAX};
 
-  for (int i = 0; i < NS - 1 && st < n_st; ++i) issue();
-  int slot = 0, kq = 0, vt = 0;
-  for (int i = 0; i < n_st; ++i) {
-    if (i + NS - 2 < n_st) {
-      wait_vmcnt<(NS - 2) * LPS>();  // only the loads of the NS - 2 next stages may still fly
+  // A stage's fragments are read whole, half a stage ahead of their use: in the
+  // middle of stage i every wave holds stage i in registers, so its slot takes
+  // the loads of stage i + NS, and the reads of stage i + 1 run under the second
+  // half's MFMAs (64 x 1024: 218.7 us with the reads and all loads at the start of
+  // their stage, 216.0 with the reads ahead, 214.3 with the loads apart).
+  bf16x8 a[2][4], bx[2][4];
+  int slot = 0, kq_n = 0;  // of the next stage to read
+  auto read_stage = [&](auto buf, bool more_loads) __attribute__((always_inline)) {
+    constexpr int F = decltype(buf)::value;
+    if (more_loads) {
+      // only the loads of the later stages already requested may still fly
+      if (wave < 4) {
+        wait_vmcnt<(NS - 2) * LPS>();
+      } else {
+        wait_vmcnt<(NS - 3) * LPS>();
+      }
     } else {
       wait_vmcnt<0>();
     }
-    if (kq == nks - 1 && rows_tail < BK) zero_k_tail(slot);
+    if (kq_n == nks - 1 && rows_tail < BK) zero_k_tail(slot);
     block_barrier();
-    if (st < n_st) issue();  // into the buffers read in the previous iteration
-
-    const int vbase = v_lo + vt * BVF + wv * 32;
-    if (vbase < v_hi) {
-      const uint32_t wa = lds_addr(lds_w[slot]) + (wv * 32 + n) * 128;
-      const uint32_t xa = lds_addr(lds_x[slot]) + (rbase + n) * 128;
-      bf16x8 a[4], bx[4];
+    const uint32_t wa = lds_addr(lds_w[0]) + slot * WTB + (wv * 32 + n) * 128;
+    const uint32_t xa = lds_addr(lds_x[0]) + slot * XTB + (rbase + n) * 128;
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const uint32_t col = ((2 * ks + hh) ^ cswz<64>(n)) << 4;
-        a[ks] = lds_read_b128<0>(wa + col);
-        bx[ks] = lds_read_b128<0>(xa + col);
-      }
-      auto step = [&](int ks) {
-        lds_tie(a[ks]);
-        lds_tie(bx[ks]);
-        const f32x4 a4 = __builtin_bit_cast(f32x4, a[ks]), b4 = __builtin_bit_cast(f32x4, bx[ks]);
-        acc[0][0] = mfma32x32x2_f32(a4[0], b4[0], acc[0][0]);
-        acc2 = mfma32x32x2_f32(a4[1], b4[1], acc2);
-        acc[0][0] = mfma32x32x2_f32(a4[2], b4[2], acc[0][0]);
-        acc2 = mfma32x32x2_f32(a4[3], b4[3], acc2);
-        __builtin_amdgcn_sched_barrier(0);
-      };
-      lds_wait<6>();
+    for (int ks = 0; ks < 4; ++ks) {
+      const uint32_t col = ((2 * ks + hh) ^ cswz<64>(n)) << 4;
+      a[F][ks] = lds_read_b128<0>(wa + col);
+      bx[F][ks] = lds_read_b128<0>(xa + col);
+    }
+    if (++kq_n == nks) kq_n = 0;
+    if (++slot == NS) slot = 0;
+  };
+
+  for (int i = 0; i < NS - 1 && st < n_st; ++i) issue();
+  read_stage(std::integral_constant<int, 0>{}, NS - 2 < n_st);
+  int kq = 0, vt = 0;
+  auto stage = [&](int i, auto buf) __attribute__((always_inline)) {
+    constexpr int F = decltype(buf)::value;
+    const int vbase = v_lo + vt * BVF + wv * 32;
+    const bool active = vbase < v_hi;
+    auto step = [&](int ks) __attribute__((always_inline)) {
+      const f32x4 a4 = __builtin_bit_cast(f32x4, a[F][ks]), b4 = __builtin_bit_cast(f32x4, bx[F][ks]);
+      acc[0][0] = mfma32x32x2_f32(a4[0], b4[0], acc[0][0]);
+      acc2 = mfma32x32x2_f32(a4[1], b4[1], acc2);
+      acc[0][0] = mfma32x32x2_f32(a4[2], b4[2], acc[0][0]);
+      acc2 = mfma32x32x2_f32(a4[3], b4[3], acc2);
+    };
+    lds_wait<0>();
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      lds_tie(a[F][ks]);
+      lds_tie(bx[F][ks]);
+    }
+    // the loads into the slot of stage i - 1, which every wave has read
+    // (waves 4-7, the second of each SIMD, do so in the other half of the stage,
+    // so that one of the two has MFMAs to issue meanwhile)
+    if (wave < 4 && st < n_st) issue();
+    __builtin_amdgcn_sched_barrier(0);
+    if (active) {
       step(0);
-      lds_wait<4>();
       step(1);
-      lds_wait<2>();
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (i + 1 < n_st) read_stage(std::integral_constant<int, F ^ 1>{}, i + NS - 1 < n_st);
+    __builtin_amdgcn_sched_barrier(0);
+    if (wave >= 4 && st < n_st) issue();
+    __builtin_amdgcn_sched_barrier(0);
+    if (active) {
       step(2);
-      lds_wait<0>();
       step(3);
+      __builtin_amdgcn_sched_barrier(0);
       if (kq == nks - 1) {
         acc[0][0] += acc2;
         fold_tile<1, 1, !SAMPLE>(acc, v_hi - vbase - 4 * hh, vbase + 4 * hh, m_run, s_run, i_run);
@@ -718,7 +750,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void s
       kq = 0;
       ++vt;
     }
-    if (++slot == NS) slot = 0;
+  };
+  for (int i = 0; i < n_st; i += 2) {
+    stage(i, std::integral_constant<int, 0>{});
+    if (i + 1 < n_st) stage(i + 1, std::integral_constant<int, 1>{});
   }
   block_barrier();  // every wave is done with the stage buffers (reused below)
   store_partials<1, BR, VW, SAMPLE>(p, n_vg, vg, row0, rbase, wv, hh, n, m_run, s_run, i_run, g_best, g_id,
