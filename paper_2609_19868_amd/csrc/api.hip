@@ -96,10 +96,21 @@ AttnPlan plan_attn(const zarya_slot_attn_desc* d) {
   // as many key tiles as the draft tokens (4B shape: 358 against 372-379 us;
   // on the 4096-token training layout, all draft tokens under a causal mask,
   // they are 6% slower)
+  const int64_t groups = (int64_t)d->batch * d->n_kv_heads;
   const int n_narrow = (pl.R + kAttnRowsPerBlock - 1) / kAttnRowsPerBlock;
   const int n_wide = (pl.R + kAttnWideRowsPerBlock - 1) / kAttnWideRowsPerBlock;
-  const bool wide = d->dtype == ZARYA_DTYPE_BF16 && 2 * n_wide <= n_narrow &&
-                    (int64_t)pl.n_prefix_tiles * kAttnKeysPerTile >= pl.T;
+  bool wide = d->dtype == ZARYA_DTYPE_BF16 && 2 * n_wide <= n_narrow &&
+              (int64_t)pl.n_prefix_tiles * kAttnKeysPerTile >= pl.T;
+  // Few of them: twice as many 128-row blocks instead, which fill the units
+  // with half the splits and give each row the result that eight splits of
+  // 256-row blocks give, bit for bit.  Up to 32 key tiles a split (16 at D = 64,
+  // whose tiles are half as long); past that the second wave of a SIMD pays.
+  // One sequence, 32/8 heads x 128 tokens, D = 128, against 16 splits of 256-row
+  // blocks: 64 tiles 27.6 and 30.7 us, 128 33.3 and 36.9, 256 52.5 and 52.7,
+  // 384 71.0 and 68.5, 512 99.9 and 83.3; 16/8 heads, 512 tiles 55.0 and 56.9,
+  // 1024 99 and 95; D = 64, 16/8 heads: 128 tiles 20.3 and 22.1, 512 41.0 and 37.8
+  if (wide && groups * n_wide <= 16)
+    wide = (int64_t)pl.n_prefix_tiles * 4 > d->head_dim * (256 / (groups * n_narrow));
   pl.rows_per_block = wide ? kAttnWideRowsPerBlock : kAttnRowsPerBlock;
   pl.n_rb = wide ? n_wide : n_narrow;
   int ns = 1;
@@ -108,13 +119,15 @@ AttnPlan plan_attn(const zarya_slot_attn_desc* d) {
       ns = d->prefix_splits;
     } else {
       // aim for about one workgroup per compute unit (measured best on the
-      // 0.6B/1.7B/4B shapes; where several splits reach it, not past it: a
-      // second workgroup on a few units doubles the longest).  A split costs
-      // its partials' round trip, so each keeps at least four key tiles, or
-      // two where that makes no more than eight splits.  One sequence, 8 x 128
-      // rows: 32 tiles 15.7 us at 8 splits, 16.7 at 16; 128 tiles 29.1 us at 8,
-      // 22.3 at 16, 20.1 at 32; 512 tiles 84.5, 50.2 and 37.3 us
-      const int64_t base = (int64_t)d->batch * d->n_kv_heads * pl.n_rb;
+      // 0.6B/1.7B/4B shapes; where several splits reach it, not past it: 16/8
+      // heads x 64 tokens, 32 tiles, 5 sequences 21.6 us with 6 splits and 25.9
+      // with 7; 9 sequences 30.5 with 3, 35.4 with 4; 96 tiles, 13 sequences 85
+      // with 2, 84 with 3).  A split costs its partials' round trip, so each
+      // keeps at least four key tiles, or two where that makes no more than
+      // eight splits.  One sequence, 8 x 128 rows: 32 tiles 15.7 us at 8 splits,
+      // 16.7 at 16; 128 tiles 27.8 us at 8, 21.7 at 16, 19.7 at 32; 512 tiles
+      // 84.5, 50.2 and 37.3 us
+      const int64_t base = groups * pl.n_rb;
       int64_t want = base <= 128 ? 256 / base : (256 + base - 1) / base;
       // long prefixes: two workgroups per compute unit when every split
       // still walks at least 64 key tiles, so that one workgroup's softmax
@@ -126,6 +139,11 @@ AttnPlan plan_attn(const zarya_slot_attn_desc* d) {
       if (pl.rows_per_block == kAttnRowsPerBlock && pl.n_prefix_tiles >= 128 * want) want *= 2;
       ns = (int)std::min<int64_t>(64, std::max<int64_t>(1, want));
       ns = std::max(1, std::min(ns, std::max(std::min(8, pl.n_prefix_tiles / 2), pl.n_prefix_tiles / 4)));
+      // more than eight cost a merge of four waves a row: only where they take
+      // three tiles off the longest walk (36 tiles: 9 splits 17.0 us, 8 15.7; 44:
+      // 11 splits 17.7, 8 16.9; 64: 16 splits 19.5, 8 20.3; three sequences, 64
+      // tiles: 10 splits 25.2, 8 24.4; 128 tiles 33.5 and 35.6)
+      if (ns > 8 && (pl.n_prefix_tiles + 7) / 8 - (pl.n_prefix_tiles + ns - 1) / ns < 3) ns = 8;
     }
     ns = std::min(ns, pl.n_prefix_tiles);
     pl.tiles_per_split = (pl.n_prefix_tiles + ns - 1) / ns;

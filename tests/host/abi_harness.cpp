@@ -192,6 +192,16 @@ static void named_plans() {
       {"modeA", 16, 16, 8, 2048, 260, 1, 1, 128, 5, 1},
       {"128-row blocks, 256 prefix tiles: two splits doubled", 16, 16, 8, 16384, 8, 8, 0, 128, 1, 4},
       {"128-row blocks, 128 prefix tiles: two splits kept", 16, 16, 8, 8192, 8, 8, 0, 128, 1, 2},
+      // few 256-row blocks: twice the 128-row ones and no more than the eight
+      // splits they had, so that the results stay what eight splits give
+      {"qwen4b batch 1", 1, 32, 8, 16384, 8, 16, 0, 128, 4, 8},
+      {"qwen4b batch 1, 8192 keys", 1, 32, 8, 8192, 8, 16, 0, 128, 4, 8},
+      {"qwen4b batch 1, 32768 keys: 64 tiles a split", 1, 32, 8, 32768, 8, 16, 0, 256, 2, 16},
+      {"qwen4b batch 2", 2, 32, 8, 16384, 8, 16, 0, 256, 2, 8},
+      // more than eight splits where they take three tiles off the longest walk
+      {"qwen0.6b batch 1, 36 tiles", 1, 16, 8, 2304, 8, 8, 0, 128, 1, 8},
+      {"qwen0.6b batch 1, 64 tiles", 1, 16, 8, 4096, 8, 8, 0, 128, 1, 16},
+      {"qwen0.6b batch 3, 64 tiles", 3, 16, 8, 4096, 8, 8, 0, 128, 1, 8},
   };
   for (const Case& c : cases) {
     zarya_slot_attn_desc d{};

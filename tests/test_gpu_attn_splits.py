@@ -31,3 +31,18 @@ def test_many_splits(splits, head_dim):
     O, L = oracle.slot_attention(xf["q"], xf["k_cache"], xf["v_cache"], xf["k_slot"], xf["v_slot"], plens, wl.n_slots,
                                  wl.slot_len, wl.scale, oracle.PASS_DIFFUSION)
     check_attn(to_f64(out), to_f64(lse), O, L, "bf16", f"splits {splits}")
+
+
+@pytest.mark.parametrize("prefix", [4096, 8192])
+def test_few_wide_blocks_give_the_result_of_eight_splits(prefix):
+    """One sequence whose 256-row blocks are few: the planner halves the blocks
+    instead of doubling the splits, which leaves every bit as eight splits of
+    256-row blocks had it."""
+    dev = require_gpu()
+    wl = W.WORKLOADS["qwen4b"].replace(batch=1, prefix_len=prefix, hidden=0, vocab=0, seed=94)
+    xd, _ = attn_inputs_dev(wl, dev)
+    say(f"slot_attn one sequence, {prefix} keys, planner's splits and eight")
+    got = [Z.slot_attn(xd["q"], xd["k_cache"], xd["v_cache"], xd["k_slot"], xd["v_slot"], wl.n_slots, wl.slot_len,
+                       prefix_len=wl.prefix_len, prefix_splits=n) for n in (0, 8)]
+    torch.cuda.synchronize()
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
