@@ -133,7 +133,9 @@ typedef struct zarya_slot_attn_desc {
                             F32 path ignores it)                             */
 } zarya_slot_attn_desc;
 
-/* Bytes of device workspace zarya_slot_attn needs for `desc` (may be 0). */
+/* Bytes of device workspace zarya_slot_attn needs for `desc` (may be 0).  With
+ * prefix_splits = 0 the size for the longest prefix_len of a call serves every
+ * shorter one. */
 zarya_status zarya_slot_attn_workspace_size(const zarya_slot_attn_desc* desc, size_t* bytes);
 
 /* Work decomposition zarya_slot_attn chooses for `desc` (diagnostics only;

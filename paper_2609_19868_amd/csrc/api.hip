@@ -99,8 +99,9 @@ AttnPlan plan_attn(const zarya_slot_attn_desc* d) {
   const int64_t groups = (int64_t)d->batch * d->n_kv_heads;
   const int n_narrow = (pl.R + kAttnRowsPerBlock - 1) / kAttnRowsPerBlock;
   const int n_wide = (pl.R + kAttnWideRowsPerBlock - 1) / kAttnWideRowsPerBlock;
-  bool wide = d->dtype == ZARYA_DTYPE_BF16 && 2 * n_wide <= n_narrow &&
-              (int64_t)pl.n_prefix_tiles * kAttnKeysPerTile >= pl.T;
+  const bool fits_wide = d->dtype == ZARYA_DTYPE_BF16 && 2 * n_wide <= n_narrow &&
+                         (int64_t)pl.n_prefix_tiles * kAttnKeysPerTile >= pl.T;
+  bool wide = fits_wide;
   // Few of them: twice as many 128-row blocks instead, which fill the units
   // with half the splits and give each row the result that eight splits of
   // 256-row blocks give, bit for bit.  Up to 32 key tiles a split (16 at D = 64,
@@ -110,7 +111,7 @@ AttnPlan plan_attn(const zarya_slot_attn_desc* d) {
   // 384 71.0 and 68.5, 512 99.9 and 83.3; 16/8 heads, 512 tiles 55.0 and 56.9,
   // 1024 99 and 95; D = 64, 16/8 heads: 128 tiles 20.3 and 22.1, 512 41.0 and 37.8
   if (wide && groups * n_wide <= 16)
-    wide = (int64_t)pl.n_prefix_tiles * 4 > d->head_dim * (256 / (groups * n_narrow));
+    wide = (int64_t)pl.n_prefix_tiles * 4 > d->head_dim * (kAttnTargetWGs / (groups * n_narrow));
   pl.rows_per_block = wide ? kAttnWideRowsPerBlock : kAttnRowsPerBlock;
   pl.n_rb = wide ? n_wide : n_narrow;
   int ns = 1;
@@ -128,7 +129,7 @@ AttnPlan plan_attn(const zarya_slot_attn_desc* d) {
       // 16.7 at 16; 128 tiles 27.8 us at 8, 21.7 at 16, 19.7 at 32; 512 tiles
       // 84.5, 50.2 and 37.3 us
       const int64_t base = groups * pl.n_rb;
-      int64_t want = base <= 128 ? 256 / base : (256 + base - 1) / base;
+      int64_t want = base <= kAttnTargetWGs / 2 ? kAttnTargetWGs / base : (kAttnTargetWGs + base - 1) / base;
       // long prefixes: two workgroups per compute unit when every split
       // still walks at least 64 key tiles, so that one workgroup's softmax
       // overlaps the other's MFMAs (4B shape, 256 tiles: 383 us with two
@@ -154,7 +155,22 @@ AttnPlan plan_attn(const zarya_slot_attn_desc* d) {
   pl.n_split = ns;
   pl.ws_bytes = 0;
   if (ns > 1) {
-    pl.ws_bytes = align256((size_t)ns * pl.rows_total * d->head_dim * 4) + align256((size_t)ns * pl.rows_total * 4);
+    // A buffer kept for the largest call has to serve the smaller ones, but the
+    // splits taken do not only grow with a call: they are rounded to equal tiles
+    // and held to the units that the row blocks leave.  So the planner's own are
+    // sized before the rounding and counted to reach the units, up to eight; from
+    // 36 tiles on, where few row blocks may get more than eight, a call has
+    // room for 256 rows of each unit, the most that come of those.
+    int64_t rows = (int64_t)ns * pl.rows_total;
+    if (d->prefix_splits == 0) {
+      const int64_t blocks = groups * (fits_wide ? n_wide : n_narrow);
+      int64_t reach = (kAttnTargetWGs + blocks - 1) / blocks;
+      if (!fits_wide && pl.n_prefix_tiles >= 128 * reach) reach *= 2;
+      reach = std::min<int64_t>(std::min<int64_t>(8, reach), pl.n_prefix_tiles / 2);
+      rows = std::max(rows, reach * pl.rows_total);
+      if (pl.n_prefix_tiles >= 36) rows = std::max<int64_t>(rows, kAttnTargetWGs * kAttnWideRowsPerBlock);
+    }
+    pl.ws_bytes = align256((size_t)rows * d->head_dim * 4) + align256((size_t)rows * 4);
   }
   return pl;
 }

@@ -165,6 +165,7 @@ constexpr int kAttnKeysPerTile = 64;
 constexpr int kAttnF32Waves = 8;            // float32 path: waves per workgroup, which split the keys
 constexpr int kAttnRowsPerBlock = 128;      // four waves
 constexpr int kAttnWideRowsPerBlock = 256;  // eight waves: every K/V tile staged once for 256 rows
+constexpr int kAttnTargetWGs = 256;         // workgroups the bf16 planner splits the prefix for: one a compute unit
 // float32 path: query rows per workgroup.  32 rows read each key half as often
 // as 16; 16 rows make twice as many workgroups, which pays where 32 leave
 // compute units idle and every wave still walks more than one 16-key tile.
