@@ -180,6 +180,7 @@ AttnPlan plan_attn(const zarya_slot_attn_desc* d) {
 struct ConfPlan {
   int n_vg, n_rt;
   int vg_split;  // workgroups per vocabulary group (1 except on the float32 path)
+  size_t ws_part;  // bytes of one partial array
   size_t ws_bytes;
 };
 
@@ -207,6 +208,7 @@ zarya_status check_conf_desc(const zarya_conf_desc* d) {
 ConfPlan plan_conf(const zarya_conf_desc* d) {
   ConfPlan pl{};
   pl.vg_split = 1;
+  bool can_split = false;
   if (d->dtype == ZARYA_DTYPE_BF16) {
     const int br = conf_tile_rows(d->n_rows);
     pl.n_rt = (d->n_rows + br - 1) / br;
@@ -224,15 +226,22 @@ ConfPlan plan_conf(const zarya_conf_desc* d) {
     const int64_t items = (int64_t)pl.n_vg * ((d->n_rows + br - 1) / br);
     const int tiles = (d->vocab + kConfF32MinIds - 1) / kConfF32MinIds;
     pl.vg_split = (int)std::max<int64_t>(1, std::min<int64_t>(kConfTargetWGs / items, tiles / pl.n_vg));
+    can_split = tiles / pl.n_vg > 1;
   }
-  pl.ws_bytes = 3 * align256((size_t)pl.n_vg * pl.vg_split * d->n_rows * 4);
+  int64_t partials = (int64_t)pl.n_vg * pl.vg_split * d->n_rows;
+  // The float32 groups are split the less the more rows there are; a buffer kept
+  // for the most rows has to serve fewer, so a vocabulary that can be split has
+  // room for what the units make of one 64-row tile.
+  if (can_split) partials = std::max<int64_t>(partials, kConfTargetWGs * 64);
+  pl.ws_part = align256((size_t)partials * 4);
+  pl.ws_bytes = 3 * pl.ws_part;
   return pl;
 }
 
 // Sampling keeps two more partial arrays (best perturbed score and its id).
 size_t sample_ws_bytes(const zarya_conf_desc* d) {
   const ConfPlan pl = plan_conf(d);
-  return pl.ws_bytes + 2 * align256((size_t)pl.n_vg * pl.vg_split * d->n_rows * 4);
+  return pl.ws_bytes + 2 * pl.ws_part;
 }
 
 // Device address of `scratch` on the current device, looked up once per
@@ -266,7 +275,7 @@ zarya_status run_conf(const zarya_conf_desc* d, const zarya_sample_params* sp, c
                       float* sample_prob, void* workspace, hipStream_t stream) {
   const ConfPlan pl = plan_conf(d);
   (void)hipGetLastError();
-  const size_t part = align256((size_t)pl.n_vg * pl.vg_split * d->n_rows * 4);
+  const size_t part = pl.ws_part;
   char* ws = static_cast<char*>(workspace);
   ConfParams p{};
   p.hidden = hidden;

@@ -29,3 +29,10 @@ def test_attention_workspace_serves_fewer_sequences(heads, S, L, P, fewer, more)
 def test_attention_workspace_serves_fewer_draft_tokens():
     # 129 tokens of two heads make three row blocks a head, 128 make one
     assert attn_bytes(1, (16, 8), 16384, 1, 129) >= attn_bytes(1, (16, 8), 16384, 1, 128) > 0
+
+
+@pytest.mark.parametrize("vocab", [100, 300, 5000, 32000, 151936])
+@pytest.mark.parametrize("size", [_lib.slot_confidence_workspace_size, _lib.slot_sample_workspace_size])
+def test_float32_head_workspace_serves_fewer_rows(size, vocab):
+    sizes = [size(_lib.ConfDesc(n_rows=M, hidden=64, vocab=vocab, dtype=_lib.DTYPE_F32)) for M in range(1, 2000)]
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
