@@ -74,7 +74,11 @@ __device__ __forceinline__ int cswz(int r) {
 // row block jb; offsets c >= lim are past the vocabulary range.  The argmax
 // is searched only when the tile raises the running maximum; the lowest id at
 // the maximum wins (earlier tiles hold lower ids).  ARGMAX = false skips it.
-template <int IB, int JB, bool ARGMAX = true>
+// DIFF: the exponentials take the difference x - m first, so that the largest
+// is 1 whatever its logit (float32 inputs).  Otherwise they are one fma each,
+// x * log2e - m * log2e, whose rounded second term moves them all by up to
+// |m| * 4e-8 of their value: 1e-5 at a logit of 300.
+template <int IB, int JB, bool ARGMAX, bool DIFF>
 __device__ __forceinline__ void fold_tile(const f32x16 (&acc)[IB][JB], int lim, int id0, float (&m_run)[JB],
                                           float (&s_run)[JB], int (&i_run)[JB]) {
   const bool full = lim >= 32 * IB;
@@ -125,14 +129,15 @@ __device__ __forceinline__ void fold_tile(const f32x16 (&acc)[IB][JB], int lim, 
       i_run[jb] = id0 + it;
     }
     const float mn = fmaxf(m_run[jb], mt);
-    const float mn2 = mn * kLog2e;
+    const float mn2 = DIFF ? mn : mn * kLog2e;
+    const auto term = [](float x, float m) { return fast_exp2(DIFF ? (x - m) * kLog2e : fmaf(x, kLog2e, -m)); };
     float e = 0.f;
     if (full) {
 #pragma unroll
       for (int ib = 0; ib < IB; ++ib) {
         float e4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int v = 0; v < 16; ++v) e4[v & 3] += fast_exp2(fmaf(acc[ib][jb][v], kLog2e, -mn2));
+        for (int v = 0; v < 16; ++v) e4[v & 3] += term(acc[ib][jb][v], mn2);
         e += (e4[0] + e4[1]) + (e4[2] + e4[3]);
         __builtin_amdgcn_sched_barrier(0);  // keep the live ranges short
       }
@@ -146,7 +151,7 @@ __device__ __forceinline__ void fold_tile(const f32x16 (&acc)[IB][JB], int lim, 
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int c = ib * 32 + 8 * (v >> 2) + (v & 3);
-          const float pe = fast_exp2(fmaf(acc[ib][jb][v], kLog2e, -mn2p));
+          const float pe = term(acc[ib][jb][v], mn2p);
           e += c < lim ? pe : 0.f;
         }
     }
@@ -533,7 +538,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
     __builtin_amdgcn_sched_barrier(0);
     if (last) {
       if (active) {
-        fold_tile<IB, JB, !SAMPLE>(acc, v_hi - vbase - 4 * hh, vbase + 4 * hh, m_run, s_run, i_run);
+        fold_tile<IB, JB, !SAMPLE, false>(acc, v_hi - vbase - 4 * hh, vbase + 4 * hh, m_run, s_run, i_run);
         if constexpr (SAMPLE)
           sample_fold<IB, JB>(acc, v_hi - vbase - 4 * hh, vbase + 4 * hh, row0 + rbase + n, p, g_best, g_id);
       }
@@ -740,7 +745,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void s
       __builtin_amdgcn_sched_barrier(0);
       if (kq == nks - 1) {
         acc[0][0] += acc2;
-        fold_tile<1, 1, !SAMPLE>(acc, v_hi - vbase - 4 * hh, vbase + 4 * hh, m_run, s_run, i_run);
+        fold_tile<1, 1, !SAMPLE, true>(acc, v_hi - vbase - 4 * hh, vbase + 4 * hh, m_run, s_run, i_run);
         if constexpr (SAMPLE)
           sample_fold<1, 1>(acc, v_hi - vbase - 4 * hh, vbase + 4 * hh, row0 + rbase + n, p, g_best, g_id);
         acc[0][0] = acc2 = f32x16{};

@@ -65,3 +65,29 @@ def test_f32_tile_edges(M, H, V, off_x, off_w):
     assert np.array_equal(sid[decided], ref["sample_id"][decided])
     p = np.exp(np.einsum("ih,ih->i", hf[rows], wf[sid]) - ref["lse"])
     assert np.abs(got["sample_prob"].cpu().numpy() - p).max() <= 1e-4 * max(1e-3, p.max())
+
+
+@pytest.mark.parametrize("M,V", [(5, 300), (64, 5001)])
+@pytest.mark.parametrize("top", [20.0, 300.0, 1000.0, -700.0])
+def test_f32_dominant_logits(top, M, V):
+    """A few logits at and just below a large maximum, the rest far away.  Every
+    logit is exact (integers times 2^-3, below 2^24 of them), so max_prob carries
+    only the rounding of the exponentials: (x - m) * log2e to 2^-24 of up to 6 log2
+    units (2.5e-7 of the term), the instruction's and the sums' few 2^-24."""
+    dev = require_gpu()
+    rng = np.random.default_rng(int(abs(top)) + V)
+    H = 36
+    w = np.zeros((V, H), np.float32)
+    w[:, 0] = 8 * (top - 100 - rng.integers(0, 400, V) / 8)
+    w[rng.choice(V, 6, replace=False), 0] = 8 * (top - np.array([0.0, 0.125, 0.5, 1.25, 2.5, 4.0]))
+    w[:, 1:] = rng.integers(-3, 4, (V, H - 1))
+    h = np.zeros((M, H), np.float32)
+    h[:, 0] = 0.125
+    say(f"slot_confidence f32 M={M} V={V} dominant logit {top}")
+    res = Z.slot_confidence(torch.from_numpy(h).to(dev), torch.from_numpy(w).to(dev))
+    torch.cuda.synchronize()
+    ref = oracle.slot_confidence(h.astype(np.float64), w.astype(np.float64))
+    p = res["max_prob"].cpu().numpy().astype(np.float64)
+    assert p.max() <= 1.0
+    assert np.abs(p / ref["max_prob"] - 1).max() <= 1e-6
+    assert np.array_equal(res["argmax"].cpu().numpy(), ref["argmax"])
