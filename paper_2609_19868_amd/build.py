@@ -8,6 +8,7 @@ from __future__ import annotations
 import concurrent.futures as cf
 import glob
 import os
+import re
 import shutil
 import subprocess
 import sys
@@ -31,6 +32,7 @@ HIPCC_FLAGS = [
     "-I", INCLUDE,
     "-I", CSRC,
 ]
+RESOURCE_FLAG = "-Rpass-analysis=kernel-resource-usage"
 
 
 def _hipcc():
@@ -44,8 +46,41 @@ def _run(cmd):
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     out = "\n".join(l for l in r.stdout.splitlines() if "packed-fp32-ops" not in l and "not a recognized feature" not in l)
     if r.returncode != 0:
-        raise RuntimeError(f"command failed ({r.returncode}): {' '.join(cmd)}\n{out}")
+        raise RuntimeError(f"command failed ({r.returncode}): {' '.join(cmd)}\n{without_remarks(out)}")
     return out
+
+
+def without_remarks(text):
+    """Compiler output without its remarks and the source lines quoted under them."""
+    keep, lines = True, []
+    for l in text.splitlines():
+        if re.search(r"(?:^|: )(remark|warning|error|note): ", l):
+            keep = "remark: " not in l
+        if keep:
+            lines.append(l)
+    return "\n".join(lines)
+
+
+def kernel_resources(text):
+    """{kernel: {field: number}} from the compiler's kernel-resource-usage remarks."""
+    kernels, name = {}, None
+    for field, value in re.findall(r"remark: +([^:\n]+): (\S+) \[-Rpass-analysis=kernel-resource-usage\]", text):
+        if field == "Function Name":
+            name = value
+            kernels[name] = {}
+        elif value.isdigit():
+            kernels[name][field] = int(value)
+    return kernels
+
+
+def check_kernels(text):
+    """Refuse kernels with scratch memory or spilled vector registers.  Their LDS
+    reads are inline assembly whose results are in flight until a later wait, which
+    the compiler does not know: a spill in between would store stale data."""
+    for name, r in kernel_resources(text).items():
+        if r["ScratchSize [bytes/lane]"] or r["VGPRs Spill"]:
+            raise RuntimeError(f"{name}: {r['ScratchSize [bytes/lane]']} bytes of scratch, "
+                               f"{r['VGPRs Spill']} spilled vector registers; no kernel may have either")
 
 
 def build(verbose: bool = False) -> str:
@@ -55,13 +90,17 @@ def build(verbose: bool = False) -> str:
     sources = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
     objs = [os.path.join(BUILD_DIR, os.path.basename(s) + ".o") for s in sources]
     with cf.ThreadPoolExecutor(max_workers=min(8, len(sources))) as ex:
-        outs = list(ex.map(lambda so: _run([hipcc, *HIPCC_FLAGS, "-c", so[0], "-o", so[1]]), zip(sources, objs)))
+        outs = list(ex.map(lambda so: _run([hipcc, *HIPCC_FLAGS, RESOURCE_FLAG, "-c", so[0], "-o", so[1]]),
+                           zip(sources, objs)))
+    for o in outs:
+        check_kernels(o)
     tmp = LIB_PATH + ".tmp"
     # -z defs: a kernel whose host launch stub was not emitted fails the link here
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-Wl,-z,defs", "-o", tmp, *objs])
     os.replace(tmp, LIB_PATH)
     if verbose:
         for o in outs:
+            o = without_remarks(o)
             if o.strip():
                 print(o)
         print(f"built {LIB_PATH}")
