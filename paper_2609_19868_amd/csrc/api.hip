@@ -375,11 +375,13 @@ zarya_status zarya_slot_attn_plan(const zarya_slot_attn_desc* desc, zarya_slot_a
   const AttnPlan pl = plan_attn(desc);
   if (desc->dtype == ZARYA_DTYPE_F32) {
     const int64_t groups = (int64_t)desc->batch * desc->n_kv_heads;
-    const int rows = attn_f32_rows_per_block(groups, pl.R, (int64_t)desc->prefix_len + pl.T);
+    const bool one_wave = attn_f32_one_wave(
+        groups, pl.R, attn_f32_keys_seen(desc->prefix_len, pl.T, desc->slot_len, desc->cross_slot));
+    const int rows = one_wave ? 16 : attn_f32_rows_per_block(groups, pl.R, (int64_t)desc->prefix_len + pl.T);
     info->prefix_splits = 1;
     info->rows_per_workgroup = rows;
     const int64_t blocks = groups * ((pl.R + rows - 1) / rows);
-    info->workgroups = (int32_t)(blocks * attn_f32_row_parts(desc->head_dim, rows, blocks));
+    info->workgroups = (int32_t)(blocks * (one_wave ? 1 : attn_f32_row_parts(desc->head_dim, rows, blocks)));
     info->kernels = 1;
     return ZARYA_OK;
   }

@@ -162,7 +162,7 @@ int64_t mask_budget_plan(int32_t n_masked, int32_t n_steps, double alpha0, uint6
 constexpr int kAppendMaxTokens = 8192;
 
 constexpr int kAttnKeysPerTile = 64;
-constexpr int kAttnF32Waves = 8;            // float32 path: waves per workgroup, which split the keys
+constexpr int kAttnF32Waves = 8;            // float32 path: waves per workgroup (or one), which split the keys
 constexpr int kAttnRowsPerBlock = 128;      // four waves
 constexpr int kAttnWideRowsPerBlock = 256;  // eight waves: every K/V tile staged once for 256 rows
 constexpr int kAttnTargetWGs = 256;         // workgroups the bf16 planner splits the prefix for: one a compute unit
@@ -171,6 +171,21 @@ constexpr int kAttnTargetWGs = 256;         // workgroups the bf16 planner split
 // compute units idle and every wave still walks more than one 16-key tile.
 constexpr int attn_f32_rows_per_block(int64_t groups, int64_t rows_per_group, int64_t keys) {
   return groups * ((rows_per_group + 31) / 32) < 256 && keys > 16 * kAttnF32Waves ? 16 : 32;
+}
+// Keys that a block of 16 rows (of at most 16 tokens) sees at most.
+constexpr int64_t attn_f32_keys_seen(int64_t prefix, int64_t tokens, int64_t slot_len, int cross) {
+  const int64_t own = cross ? tokens : 16 + 2 * slot_len;
+  return prefix + (own < tokens ? own : tokens);
+}
+// Workgroups of one wave and 16 rows instead: 1024 blocks of 16 rows fill the
+// units (4 rows x 516 keys, D = 128, eight waves and one: 1024 blocks 137 and
+// 100 us, 512 blocks 70 and 65; 128 rows x 576 keys a group, 1024 blocks 69 and
+// 69, but 2112 keys 197 and 217: there 32 rows share each key), or fewer with
+// one or two key tiles, of which eight waves would leave most without one
+// (512 blocks x 16 keys 18.5 and 14.0; 32 blocks 10.3 and 10.8).
+constexpr bool attn_f32_one_wave(int64_t groups, int64_t rows_per_group, int64_t keys_seen) {
+  const int64_t blocks = groups * ((rows_per_group + 15) / 16);
+  return (blocks >= 1024 && keys_seen <= 512) || (blocks >= 512 && keys_seen <= 32);
 }
 // Workgroups per row block.  With 16 rows and at most half a workgroup per
 // compute unit two share a block: each computes all of the scores and half of

@@ -515,10 +515,10 @@ __global__ __launch_bounds__(256) void slot_attn_merge_kernel(const float* __res
   if (lse && c == 0) lse[row] = (mx + __log2f(wsum)) * kLn2;
 }
 
-// float32 path.  One workgroup = 8 waves = 16 * NR query rows of one GQA group
+// float32 path.  One workgroup = NW waves = 16 * NR query rows of one GQA group
 // (token-major, as above); the waves share the rows and split the keys: wave w
-// takes the 16-key tiles w, w + 8, ... of the prefix and the draft tokens and
-// keeps its own online softmax; the eight partials meet in LDS and are merged
+// takes the 16-key tiles w, w + NW, ... of the prefix and the draft tokens and
+// keeps its own online softmax; the partials meet in LDS and are merged
 // in wave order, so no workspace and no second launch is needed.
 //
 // The products are v_mfma_f32_16x16x4_f32 (float32 operands and accumulators).
@@ -537,10 +537,15 @@ __global__ __launch_bounds__(256) void slot_attn_merge_kernel(const float* __res
 // with one workgroup a block; one key at a time with a shuffled dot product per
 // row, as it was at first, took 771 us.  Keys and values requested a whole tile
 // ahead (182 registers) took 26.7.
-template <int D, int NR, int DS>
-__global__ __launch_bounds__(kAttnF32Waves * 64) __attribute__((amdgpu_waves_per_eu(2))) void slot_attn_f32_kernel(
-    AttnParams32 p) {
-  constexpr int NW = kAttnF32Waves;
+//
+// NW = 1: a workgroup of one wave walks all the tiles of its rows, for launches
+// of so many row blocks that the waves fill the units without splitting keys, or
+// of so few keys that there is nothing to split: eight waves would pay a
+// workgroup's barriers and LDS, one or two workgroups a unit, for a tile each.
+// 4096 groups, D = 128: 1 row x 1 key 112 us with eight waves, 18 with one; 4 rows
+// x 68 keys 165 and 70; 4 rows x 516 keys 529 and 387.
+template <int D, int NR, int DS, int NW>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) void slot_attn_f32_kernel(AttnParams32 p) {
   constexpr int RB = 16 * NR;   // query rows per workgroup
   constexpr int NKS = D / 16;   // 16-byte pieces of a K row per lane
   constexpr int DO = D / DS;    // elements of the output row taken by this workgroup
@@ -818,9 +823,9 @@ hipError_t launch_slot_attn_bf16(const AttnParams& p, int head_dim, hipStream_t 
   return hipGetLastError();
 }
 
-template <int D, int NR, int DS>
+template <int D, int NR, int DS, int NW = kAttnF32Waves>
 void launch_attn_f32_as(const AttnParams32& p, int blocks, hipStream_t stream) {
-  slot_attn_f32_kernel<D, NR, DS><<<dim3(8 * ((DS * blocks + 7) / 8)), dim3(kAttnF32Waves * 64), 0, stream>>>(p);
+  slot_attn_f32_kernel<D, NR, DS, NW><<<dim3(8 * ((DS * blocks + 7) / 8)), dim3(NW * 64), 0, stream>>>(p);
 }
 
 template <int NR>
@@ -837,7 +842,14 @@ void launch_attn_f32_rows(const AttnParams32& p, int head_dim, int n_rb, hipStre
 
 hipError_t launch_slot_attn_f32(const AttnParams32& p, int head_dim, hipStream_t stream) {
   const int R = p.G * p.T, rows = attn_f32_rows_per_block(p.B * (int64_t)p.Hkv, R, (int64_t)p.P + p.T);
-  if (rows == 32) {
+  if (attn_f32_one_wave(p.B * (int64_t)p.Hkv, R, attn_f32_keys_seen(p.P, p.T, p.L, p.cross))) {
+    const int blocks = p.B * p.Hkv * ((R + 15) / 16);
+    if (head_dim == 64) {
+      launch_attn_f32_as<64, 1, 1, 1>(p, blocks, stream);
+    } else {
+      launch_attn_f32_as<128, 1, 1, 1>(p, blocks, stream);
+    }
+  } else if (rows == 32) {
     launch_attn_f32_rows<2>(p, head_dim, (R + 31) / 32, stream);
   } else {
     launch_attn_f32_rows<1>(p, head_dim, (R + 15) / 16, stream);

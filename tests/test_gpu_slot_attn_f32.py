@@ -100,3 +100,34 @@ def test_f32_values_a_row_does_not_see_do_not_reach_it(head_dim, prefix_len):
     assert (out[:, :, keep] - clean_out[:, :, keep]).norm() <= 1e-5 * clean_out[:, :, keep].norm()
     assert torch.equal(lse[:, :, keep], clean_lse[:, :, keep])
     assert out[:, :, 8:12].isnan().all()
+
+
+@pytest.mark.parametrize("name,over,one_wave", [
+    ("blocks512_one_tile", dict(batch=64, prefix_len=0, n_slots=3, slot_len=5), True),
+    ("blocks512_two_tiles_d64", dict(batch=64, head_dim=64, prefix_len=31, n_slots=1, slot_len=1), True),
+    ("blocks512_33_keys", dict(batch=64, prefix_len=32, n_slots=1, slot_len=1), False),
+    ("blocks504", dict(batch=63, prefix_len=0, n_slots=1, slot_len=1), False),
+    ("blocks1024_causal", dict(batch=64, head_dim=64, prefix_len=80, n_slots=32, slot_len=1), True),
+    ("blocks1024_512_keys", dict(batch=128, prefix_len=510, n_slots=2, slot_len=1), True),
+    ("blocks1024_513_keys", dict(batch=128, prefix_len=511, n_slots=2, slot_len=1), False),
+])
+def test_f32_many_blocks_take_one_wave_each(name, over, one_wave):
+    """Workgroups of one wave from 1024 blocks of 16 rows (512 with one or two key
+    tiles): both sides of the lines, 8/8 heads, ragged prefixes."""
+    dev = require_gpu()
+    wl = W.WORKLOADS["qwen0.6b"].replace(**over, n_q_heads=8, n_kv_heads=8, dtype="f32", hidden=0, vocab=0, seed=96)
+    xd, xf = attn_inputs_dev(wl, dev)
+    cross = Z.CROSS_SLOT_CAUSAL if "causal" in name else Z.CROSS_SLOT_NONE
+    S, L, P = wl.n_slots, wl.slot_len, wl.prefix_len
+    cache = [xd["k_cache"], xd["v_cache"]] if P else [None, None]
+    plan = Z._lib.slot_attn_plan(Z.slot_attn_desc(xd["q"], cache[0], xd["k_slot"], S, L, cross_slot=cross, prefix_len=P))
+    blocks16 = wl.batch * 8 * -(-S * L // 16)
+    assert (plan["rows_per_workgroup"] == 16 and plan["workgroups"] == blocks16) == one_wave
+    plens = (P - 7 * np.arange(wl.batch)).clip(0).astype(np.int32)
+    say(f"slot_attn f32 {name}")
+    out, lse = Z.slot_attn(xd["q"], *cache, xd["k_slot"], xd["v_slot"], S, L, cross_slot=cross, prefix_len=P,
+                           prefix_lens=torch.from_numpy(plens).to(dev))
+    torch.cuda.synchronize()
+    O, Ls = oracle.slot_attention(xf["q"], xf["k_cache"], xf["v_cache"], xf["k_slot"], xf["v_slot"], plens, S, L,
+                                  wl.scale, oracle.PASS_DIFFUSION, cross_slot=cross)
+    assert check_attn(to_f64(out), to_f64(lse), O, Ls, "f32", name) <= 1e-5
