@@ -46,6 +46,7 @@ struct AttnParams32 {
   int pass, cross;
   float scale;
   int rows_total;
+  int item0, n_items;  // work items of this launch (set by the launcher)
 };
 
 // LM-head confidence.  Partials are per (vocab group, row): m = max logit,
@@ -163,6 +164,9 @@ constexpr int kAppendMaxTokens = 8192;
 
 constexpr int kAttnKeysPerTile = 64;
 constexpr int kAttnF32Waves = 8;            // float32 path: waves per workgroup (or one), which split the keys
+// Largest grid of a launch whose workgroups grow with the rows: a grid holds
+// fewer than 2^32 threads, so more workgroups than this take several launches.
+constexpr int kAttnMaxGrid = 1 << 20;
 constexpr int kAttnRowsPerBlock = 128;      // four waves
 constexpr int kAttnWideRowsPerBlock = 256;  // eight waves: every K/V tile staged once for 256 rows
 constexpr int kAttnTargetWGs = 256;         // workgroups the bf16 planner splits the prefix for: one a compute unit

@@ -26,6 +26,7 @@
 //    and a merge kernel combines them exactly.  With one split the kernel
 //    writes the final bf16 output itself.  The draft tokens' own keys are
 //    processed by the last split, with the mask applied per element.
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -450,12 +451,12 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(ZARY
 template <int D, int SW>
 __global__ __launch_bounds__(256) void slot_attn_merge_kernel(const float* __restrict__ part_o,
                                                               const float* __restrict__ part_lse, int n_split,
-                                                              int rows_total, uint16_t* __restrict__ out,
+                                                              int rows_total, int row0, uint16_t* __restrict__ out,
                                                               float* __restrict__ lse) {
   constexpr int LPR = D / 4, RPW = 64 / LPR;
   constexpr int MAXS = SW == 1 ? 8 : 16;  // splits of a wave, all loaded before any arithmetic
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int row_in = (SW == 1 ? blockIdx.x * 4 + wave : blockIdx.x) * RPW + lane / LPR;
+  const int row_in = row0 + (SW == 1 ? blockIdx.x * 4 + wave : blockIdx.x) * RPW + lane / LPR;
   const int row = min(row_in, rows_total - 1);  // lanes past the end follow the last row and store nothing
   const int c = (lane % LPR) * 4;
   const int per = SW == 1 ? n_split : (n_split + SW - 1) / SW;
@@ -558,8 +559,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   __shared__ float part_m[NW][RB], part_l[NW][RB];
 
   const int n_rb = (p.G * p.T + RB - 1) / RB;
-  const int w = xcd_work_index(blockIdx.x, gridDim.x >> 3, p.B * p.Hkv * n_rb * DS);
-  if (w < 0) return;
+  const int w = xcd_work_index(blockIdx.x, gridDim.x >> 3, p.n_items) + p.item0;
+  if (w < p.item0) return;
   const int d0 = (w % DS) * DO;  // first element taken
   const int rb = w / DS % n_rb, bg = w / (DS * n_rb);
   const int b = bg / p.Hkv;
@@ -790,10 +791,13 @@ void launch_attn_merge(const AttnParams& p, hipStream_t stream) {
   constexpr int RPW = 64 / (D / 4);  // rows per wave
   if (p.n_split <= 8) {
     slot_attn_merge_kernel<D, 1><<<dim3((p.rows_total + 4 * RPW - 1) / (4 * RPW)), dim3(256), 0, stream>>>(
-        p.part_o, p.part_lse, p.n_split, p.rows_total, p.out, p.lse);
+        p.part_o, p.part_lse, p.n_split, p.rows_total, 0, p.out, p.lse);
   } else {
-    slot_attn_merge_kernel<D, 4><<<dim3((p.rows_total + RPW - 1) / RPW), dim3(256), 0, stream>>>(
-        p.part_o, p.part_lse, p.n_split, p.rows_total, p.out, p.lse);
+    for (int64_t row0 = 0; row0 < p.rows_total; row0 += (int64_t)kAttnMaxGrid * RPW) {
+      const int blocks = (int)std::min<int64_t>((p.rows_total - row0 + RPW - 1) / RPW, kAttnMaxGrid);
+      slot_attn_merge_kernel<D, 4><<<dim3(blocks), dim3(256), 0, stream>>>(p.part_o, p.part_lse, p.n_split,
+                                                                           p.rows_total, (int)row0, p.out, p.lse);
+    }
   }
 }
 
@@ -824,8 +828,13 @@ hipError_t launch_slot_attn_bf16(const AttnParams& p, int head_dim, hipStream_t 
 }
 
 template <int D, int NR, int DS, int NW = kAttnF32Waves>
-void launch_attn_f32_as(const AttnParams32& p, int blocks, hipStream_t stream) {
-  slot_attn_f32_kernel<D, NR, DS, NW><<<dim3(8 * ((DS * blocks + 7) / 8)), dim3(NW * 64), 0, stream>>>(p);
+void launch_attn_f32_as(AttnParams32 p, int blocks, hipStream_t stream) {
+  const int64_t items = (int64_t)DS * blocks;
+  for (int64_t i = 0; i < items; i += kAttnMaxGrid) {
+    p.item0 = (int)i;
+    p.n_items = (int)std::min<int64_t>(items - i, kAttnMaxGrid);
+    slot_attn_f32_kernel<D, NR, DS, NW><<<dim3(8 * ((p.n_items + 7) / 8)), dim3(NW * 64), 0, stream>>>(p);
+  }
 }
 
 template <int NR>
