@@ -13,6 +13,8 @@
 // one workgroup of 1024 threads per batch row takes each step for the whole row
 // at once: a thread per list entry, a thread per token, and for the counts and
 // positions a power of two of lanes per slot.
+#include <algorithm>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -20,7 +22,7 @@ namespace zarya {
 
 namespace {
 
-constexpr int kThreads = 1024;  // one per slot at the largest S
+constexpr int kThreads = 1024;  // at most: one per slot at the largest S
 
 }  // namespace
 
@@ -28,24 +30,38 @@ constexpr int kThreads = 1024;  // one per slot at the largest S
 // passing tokens (its length is the lowest failing position) or, token by
 // token, every passing one.  B = 16, 8 slots of 8 tokens: 6.6 -> 3.4 us (a
 // thread per slot walked its tokens, waiting for each).
-__global__ __launch_bounds__(kThreads) void verify_accept_kernel(AcceptParams p) {
+template <int MAXT>
+__global__ __launch_bounds__(MAXT) void verify_accept_kernel(AcceptParams p) {
   __shared__ int listed[1024], run[1024], count[1024];
   __shared__ int end, total;
-  const int b = blockIdx.x, tid = threadIdx.x;
-  const int mine = tid < p.S ? p.selected[(size_t)b * p.S + tid] : 0;
+  const int b = blockIdx.x, tid = threadIdx.x, threads = MAXT == kThreads ? kThreads : blockDim.x;
+  const int32_t* sel = p.selected + (size_t)b * p.S;
+  const int mine = tid < p.S ? sel[tid] : 0;
+  // f(i, list entry i) over the list, f(s, 0) over the slots: a thread each with kThreads
+  auto each = [&](int n, bool entries, auto&& f) {
+    if constexpr (MAXT == kThreads) {
+      if (tid < n) f(tid, mine);
+    } else {
+      for (int i = tid; i < n; i += threads) f(i, entries ? sel[i] : 0);
+    }
+  };
   if (tid == 0) {
     end = p.S;
     total = 0;
   }
-  listed[tid] = 0;
-  run[tid] = p.L;
-  count[tid] = 0;
+  each(p.S, false, [&](int s, int) {
+    listed[s] = 0;
+    run[s] = p.L;
+    count[s] = 0;
+  });
   __syncthreads();
   // integer minima and sums in LDS: order-free
-  if (mine < 0) atomicMin(&end, tid);  // the first negative entry ends the list
+  each(p.S, true, [&](int i, int s) {
+    if (s < 0) atomicMin(&end, i);  // the first negative entry ends the list
+  });
   const float* tp = p.token_prob + (size_t)b * p.S * p.L;
   const int T = p.S * p.L;
-  for (int x = tid; x < T; x += kThreads) {
+  for (int x = tid; x < T; x += threads) {
     const int s = x / p.L;
     if (tp[x] > p.threshold) {
       if (p.rule != 0) atomicAdd(&count[s], 1);
@@ -54,18 +70,20 @@ __global__ __launch_bounds__(kThreads) void verify_accept_kernel(AcceptParams p)
     }
   }
   __syncthreads();
-  if (tid < end && mine < p.S) listed[mine] = 1;  // ids >= S are skipped
+  each(end, true, [&](int, int s) {
+    if (s < p.S) listed[s] = 1;  // ids >= S are skipped
+  });
   __syncthreads();
   uint8_t* acc = p.accepted + (size_t)b * T;
-  for (int x = tid; x < T; x += kThreads) {
+  for (int x = tid; x < T; x += threads) {
     const int s = x / p.L;
     acc[x] = listed[s] && (p.rule == 0 ? x - s * p.L < run[s] : tp[x] > p.threshold) ? 1 : 0;
   }
-  if (tid < p.S) {
-    const int n = listed[tid] ? (p.rule == 0 ? run[tid] : count[tid]) : 0;
-    p.n_accepted[(size_t)b * p.S + tid] = n;
+  each(p.S, false, [&](int s, int) {
+    const int n = listed[s] ? (p.rule == 0 ? run[s] : count[s]) : 0;
+    p.n_accepted[(size_t)b * p.S + s] = n;
     if (n) atomicAdd(&total, n);
-  }
+  });
   __syncthreads();
   if (tid == 0 && p.n_total) p.n_total[b] = total;
 }
@@ -169,7 +187,16 @@ __global__ __launch_bounds__(kThreads) void kv_append_kernel(AppendParams p, int
 }
 
 hipError_t launch_verify_accept(const AcceptParams& p, hipStream_t stream) {
-  verify_accept_kernel<<<dim3(p.B), dim3(kThreads), 0, stream>>>(p);
+  // 1024 threads a row, of which a unit holds two, where the rows alone do not
+  // fill the units; with many rows up to 256 and no more than tokens (4096 rows: 64
+  // slots of one token 25.0 us with 1024 threads, 8.5 with 64; 256 slots of 4 39.1
+  // and 19.5 with 256; 512 rows 7.3 and 7.7)
+  if (p.B < 1024) {
+    verify_accept_kernel<kThreads><<<dim3(p.B), dim3(kThreads), 0, stream>>>(p);
+  } else {
+    const int threads = (int)std::min<int64_t>(256, ((int64_t)p.S * p.L + 63) / 64 * 64);
+    verify_accept_kernel<256><<<dim3(p.B), dim3(threads), 0, stream>>>(p);
+  }
   return hipGetLastError();
 }
 

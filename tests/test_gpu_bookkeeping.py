@@ -74,3 +74,22 @@ def test_reveal_sizes(N):
         for b in range(B):
             left[b, ref[0][b][:ref[1][b]]] = 0
         assert np.array_equal(md.cpu().numpy(), left)
+
+
+@pytest.mark.parametrize("S,L", [(1, 1), (3, 21), (13, 5), (64, 4), (257, 1), (300, 3), (1024, 2)])
+@pytest.mark.parametrize("B", [1023, 1024])
+def test_accept_of_many_rows(B, S, L):
+    """From 1024 rows a row has at most 256 threads: sizes around a wave, that
+    limit and the slots; lists that end early, name ids past S and repeat."""
+    dev = require_gpu()
+    rng = np.random.default_rng(B + 10 * S + L)
+    prob = rng.random((B, S, L)).astype(np.float32) ** np.float32(0.2)
+    prob[rng.random((B, S, L)) < 0.05] = np.nan
+    sel = rng.integers(-1 if S > 2 else 0, S + 2, (B, S)).astype(np.int32)
+    sel[B // 2:][sel[B // 2:] < 0] = 0
+    for rule in (Z.ACCEPT_PREFIX, Z.ACCEPT_PER_TOKEN):
+        say(f"verify_accept B={B} S={S} L={L} rule={rule}")
+        got = Z.verify_accept(torch.from_numpy(prob).to(dev), torch.from_numpy(sel).to(dev), 0.4, rule)
+        torch.cuda.synchronize()
+        for g, r in zip(got, oracle.accept_tokens(prob, sel, np.float32(0.4), rule)):
+            assert np.array_equal(g.cpu().numpy(), r)
