@@ -73,9 +73,13 @@ __host__ __device__ constexpr int swz(int kr) {
 
 // NWAVE: waves per workgroup, 32 query rows each; every wave stages its share
 // of each K/V tile, one tile ahead (two LDS buffers of 32 KB at D = 128, which
-// leaves room for two workgroups per CU).
+// leaves room for two workgroups per CU).  At D = 64 four waves of a SIMD fit if
+// the kernel keeps to 128 registers, which short prefixes of many sequences need
+// (71 x 8 groups of 153 rows, 470 keys: 43.4 us, and 54.6 with the 154 registers
+// and three waves that the compiler takes when it is left to).
 template <int D, int NWAVE>
-__global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(ZARYA_ATTN_WPE))) void slot_attn_bf16_kernel(AttnParams p) {
+__global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : ZARYA_ATTN_WPE))) void slot_attn_bf16_kernel(
+    AttnParams p) {
   constexpr int RB = NWAVE * 32;        // query rows per workgroup
   constexpr int ROWB = D * 2;           // bytes per key row
   constexpr int TILEB = KT * ROWB;      // bytes of one K (or V) tile
@@ -408,7 +412,16 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(ZARY
   // ---- finalize: combine the two lane halves' partial sums
   const float l_tot = sum_xor32(l_run);
   if (!row_ok) return;
-  const size_t grow = (size_t)bg * p.R + mrow;  // row of the [B*Hq*T] output
+  int orow_in = mrow;
+  if constexpr (D == 64) {
+    // worked out anew, from a thread index that the compiler does not know to be
+    // the same, instead of kept in a register through the loop
+    int te = tid;
+    asm volatile("" : "+v"(te));
+    const int row_e = rb * RB + (te >> 6) * 32 + (te & 31);
+    orow_in = (row_e % p.G) * p.T + row_e / p.G;
+  }
+  const size_t grow = (size_t)bg * p.R + orow_in;  // row of the [B*Hq*T] output
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
   const float lse2 = m_run * c2 + __log2f(l_tot);  // log2 units
   if (p.n_split == 1) {

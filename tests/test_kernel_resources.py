@@ -41,3 +41,8 @@ def test_present_kernels_are_seen_and_sound(source, kernel, at_least):
     r = device_resources(source)
     assert sum(kernel in k for k in r) >= at_least  # every instantiation is looked at
     assert all("VGPRs" in v for v in r.values())
+
+
+def test_attention_of_64_elements_fits_four_waves_a_simd():
+    r = {k: v for k, v in device_resources("slot_attn").items() if "slot_attn_bf16_kernelILi64E" in k}
+    assert len(r) == 2 and all(v["VGPRs"] + v["AGPRs"] <= 128 for v in r.values())
