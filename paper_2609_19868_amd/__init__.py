@@ -78,14 +78,23 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+def _public_raw_stream(index):
+    return torch.cuda.current_stream(index).cuda_stream
+
+
+# The handle of a device's current stream without a Stream object around it,
+# where this torch has that (it is not part of its documented interface).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", _public_raw_stream)
+
+
 def _call(fn, dev, *args):
     """fn(*args, current stream of dev) with dev current, since the library
     launches on the current device; raises on an error status."""
     if torch.cuda.current_device() == dev.index:
-        status = fn(*args, torch._C._cuda_getCurrentRawStream(dev.index))
+        status = fn(*args, _raw_stream(dev.index))
     else:
         with torch.cuda.device(dev):
-            status = fn(*args, torch._C._cuda_getCurrentRawStream(dev.index))
+            status = fn(*args, _raw_stream(dev.index))
     if status != _lib.OK:
         _lib.check(status)
 
