@@ -38,12 +38,14 @@ static bool in_ws(const void* p, size_t bytes) {
 static int g_launches = 0;
 
 namespace zarya {
+static int g_many_splits = 0;   // bf16 attention launches of more than eight splits
 static AttnParams g_last_attn;  // the parameters of the last bf16 attention launch
 
 hipError_t launch_slot_attn_bf16(const AttnParams& p, int head_dim, hipStream_t) {
   ++g_launches;
   g_last_attn = p;
   CHECK(p.n_split >= 1 && p.n_split <= 64);
+  if (p.n_split > 8) ++g_many_splits;
   CHECK((int64_t)p.tiles_per_split * p.n_split >= p.n_prefix_tiles);
   CHECK(p.n_split == 1 || (int64_t)p.tiles_per_split * (p.n_split - 1) < p.n_prefix_tiles);
   CHECK(p.rows_per_block == kAttnRowsPerBlock || p.rows_per_block == kAttnWideRowsPerBlock);
@@ -70,14 +72,21 @@ hipError_t launch_slot_attn_f32(const AttnParams32& p, int, hipStream_t) {
 }
 
 static void check_conf(const ConfParams& p) {
-  const size_t n = (size_t)p.n_vg * p.M * 4;
+  CHECK(p.vg_split >= 1 && p.n_vg * p.vg_split <= kConfMaxGroups);
+  const size_t n = (size_t)p.n_vg * p.vg_split * p.M * 4;
   CHECK(in_ws(p.part_m, n) && in_ws(p.part_s, n) && in_ws(p.part_idx, n));
+  // and do not overlap
+  const uintptr_t a[5] = {(uintptr_t)p.part_m, (uintptr_t)p.part_s, (uintptr_t)p.part_idx, (uintptr_t)p.part_g,
+                          (uintptr_t)p.part_gi};
+  for (int i = 0; i + 1 < (p.part_g ? 5 : 3); ++i) CHECK(a[i] + n <= a[i + 1]);
   if (p.part_g) CHECK(in_ws(p.part_g, n) && in_ws(p.part_gi, n));
   CHECK(p.n_vg >= 1);
   CHECK(p.n_items == p.n_vg * p.n_rt);
   CHECK(p.per_xcd * 8 >= p.n_items);
   CHECK(p.row_index != nullptr || p.hidden_rows == p.M);
 }
+
+static int g_f32_split = 0;     // float32 launches whose groups are split
 
 static ConfParams g_last_conf;  // the parameters of the last bf16 LM-head launch
 
@@ -87,14 +96,15 @@ hipError_t launch_slot_conf_bf16(const ConfParams& p, hipStream_t) {
   check_conf(p);
   CHECK(p.w_stream == 0 || p.w_stream == 1);
   CHECK((int64_t)p.n_rt * conf_tile_rows(p.M) >= p.M);
-  CHECK(p.n_vg <= (p.V + 31) / 32);
+  CHECK(p.n_vg <= (p.V + 31) / 32 && p.vg_split == 1);
   return hipErrorNoDevice;
 }
 
 hipError_t launch_slot_conf_f32(const ConfParams& p, hipStream_t) {
   ++g_launches;
   check_conf(p);
-  CHECK(p.n_rt == 1 && p.n_vg <= 64);
+  CHECK(p.n_rt == 1 && p.n_vg <= 64 && p.n_vg * p.vg_split <= (p.V + 31) / 32);
+  if (p.vg_split > 1) ++g_f32_split;
   return hipErrorNoDevice;
 }
 
@@ -142,7 +152,7 @@ static void attn_cases(std::mt19937_64& rng) {
   const int dims[2] = {64, 128};
   for (int it = 0; it < 400; ++it) {
     zarya_slot_attn_desc d{};
-    d.batch = 1 + (int)(rng() % 32);
+    d.batch = 1 + (int)(rng() % (rng() % 2 ? 32 : 3));  // small batches: the planner's own many splits
     d.n_kv_heads = 1 + (int)(rng() % 8);
     d.n_q_heads = d.n_kv_heads * (1 + (int)(rng() % 4));
     d.head_dim = dims[rng() % 2];
@@ -154,7 +164,7 @@ static void attn_cases(std::mt19937_64& rng) {
     d.pass = (int)(rng() % 2);
     d.cross_slot = (int)(rng() % 2);
     d.dtype = (rng() % 5 == 0) ? ZARYA_DTYPE_F32 : ZARYA_DTYPE_BF16;
-    d.prefix_splits = (rng() % 3 == 0) ? (int)(rng() % 9) : 0;
+    d.prefix_splits = (rng() % 3 == 0) ? (int)(rng() % 65) : 0;
     size_t ws = 0;
     CHECK(zarya_slot_attn_workspace_size(&d, &ws) == ZARYA_OK);
     g_ws_lo = 0x100000000ull;
@@ -247,7 +257,7 @@ static void conf_cases(std::mt19937_64& rng) {
   for (int it = 0; it < 400; ++it) {
     zarya_conf_desc d{};
     d.dtype = (rng() % 4 == 0) ? ZARYA_DTYPE_F32 : ZARYA_DTYPE_BF16;
-    d.n_rows = 1 + (int)(rng() % 5000);
+    d.n_rows = 1 + (int)(rng() % (rng() % 2 ? 5000 : 150));  // few rows: the float32 groups are split
     d.hidden = 8 * (1 + (int)(rng() % 512));
     d.vocab = 1 + (int)(rng() % 200000);
     size_t ws = 0, ws_s = 0;
@@ -370,6 +380,7 @@ int main() {
   conf_cases(rng);
   small_call_cases();
   budget_cases(rng);
+  CHECK(zarya::g_many_splits > 50 && zarya::g_f32_split > 50);
   std::printf("%d checks, %d failures, %d launches reached\n", g_checks, g_fail, g_launches);
   return g_fail == 0 ? 0 : 1;
 }
