@@ -54,3 +54,10 @@ def test_bf16_stage_edges(M, H, V, off):
     ids = got["sample_id"].cpu().numpy()
     z = np.einsum("ij,ij->i", hf, wf[ids])
     np.testing.assert_allclose(got["sample_prob"].cpu().numpy(), np.exp(z - ref["lse"]), rtol=1e-3)
+    # the draws themselves, on rows at the edges of the row tiles and blocks: the
+    # best score is decided where it leads by more than the logits' rounding
+    rows = np.unique(np.minimum([0, 1, 24, 31, 32, 63, 64, 127, 128, 255, 256, 299], M - 1))
+    draw = oracle.slot_sample(hf[rows], wf, 0.9, 4321, 3, row_ids=rows)
+    decided = draw["score_gap"] >= 1e-3 / 0.9
+    assert decided.sum() >= 0.9 * len(rows)
+    assert np.array_equal(ids[rows][decided], draw["sample_id"][decided])
