@@ -1,6 +1,7 @@
 """Selection, acceptance, append and reveal at the sizes where their work
 splitting can go wrong (slot lengths around the lanes per slot, slot counts
-around a wave, sorts around a wave's 128 keys): bit-exact against the oracle."""
+around a wave, reveals around the 512 positions up to which keys are counted and
+above which they are sorted): bit-exact against the oracle."""
 
 import numpy as np
 import pytest
@@ -53,13 +54,15 @@ def test_commit_sizes(S, L):
                 assert np.array_equal(g.cpu().view(torch.int16).numpy().view(np.uint16), r)
 
 
-@pytest.mark.parametrize("N", [1, 64, 127, 128, 129, 256, 257, 1025, 4096, 8192])
+@pytest.mark.parametrize("N", [1, 2, 3, 64, 127, 128, 129, 256, 257, 511, 512, 513, 1025, 4096, 8192])
 def test_reveal_sizes(N):
     dev = require_gpu()
     rng = np.random.default_rng(N)
     B = 3
     conf = rng.random((B, N)).astype(np.float32)
     conf[rng.random((B, N)) < 0.3] = np.float32(0.25)  # ties
+    odd = rng.random((B, N)) < 0.3  # NaN counts as -inf, -0 as 0
+    conf[odd] = rng.choice(np.array([np.nan, np.inf, -np.inf, 0.0, -0.0], np.float32), odd.sum())
     mask = (rng.random((B, N)) < 0.7).astype(np.uint8)
     mask[0] = 1
     k = np.array([N, max(1, N // 3), 2], np.int32)
