@@ -1,5 +1,5 @@
-"""Row blocks that are only partly filled: waves without a row, and the place of
-a small last block in the heaviest-first order, against the float64 oracle.
+"""Row blocks that are only partly filled: waves without a row, which only load,
+with and without the heaviest-first order, against the float64 oracle.
 Tolerances as in test_gpu_slot_attn.py."""
 
 import pytest
@@ -17,8 +17,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("prefix_len", [0, 40, 700])
 @pytest.mark.parametrize("heads,n_slots,slot_len", [
     ((8, 4), 66, 1),    # 132 rows: a last block of 4, one wave
-    ((8, 4), 10, 16),   # 320 rows: a last block of 64, the largest that moves
-    ((8, 4), 97, 1),    # 194 rows: 66, one more wave: keeps its place
+    ((8, 4), 10, 16),   # 320 rows: a last block of 64, two waves
+    ((8, 4), 97, 1),    # 194 rows: a last block of 66, three waves
     ((16, 4), 5, 8),    # 160 rows: 256-row block with three empty waves, or a last block of 32
     ((12, 4), 1, 11),   # 33 rows: one block, two waves
 ])
