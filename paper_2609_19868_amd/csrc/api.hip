@@ -220,7 +220,7 @@ ConfPlan plan_conf(const zarya_conf_desc* d) {
     pl.n_rt = 1;
     pl.n_vg = std::max(1, std::min(64, d->vocab / 2048));
     // with few row tiles each group is shared by several workgroups, up to
-    // about one workgroup per compute unit and 128 ids each (a group per
+    // about one workgroup per compute unit or 128 ids each (a group per
     // workgroup left three quarters of the units idle at 64 rows)
     const int br = conf_f32_tile_rows(d->n_rows);
     const int64_t items = (int64_t)pl.n_vg * ((d->n_rows + br - 1) / br);

@@ -172,7 +172,10 @@ constexpr int kAttnWideRowsPerBlock = 256;  // eight waves: every K/V tile stage
 constexpr int kAttnTargetWGs = 256;         // workgroups the bf16 planner splits the prefix for: one a compute unit
 // float32 path: query rows per workgroup.  32 rows read each key half as often
 // as 16; 16 rows make twice as many workgroups, which pays where 32 leave
-// compute units idle and every wave still walks more than one 16-key tile.
+// compute units idle (16/8 heads x 64 tokens, D = 128, 16 and 32 rows: 2048 keys,
+// 64 blocks of 32 rows 47 and 93 us, 128 blocks 61 and 95, 256 blocks 116 and 97;
+// 128 keys, 64 blocks 9.0 and 16.3).  Up to 128 keys, one tile a wave, 32 rows are
+// taken, which is not the faster side (64 + 64 keys 7.8 and 12.1 us).
 constexpr int attn_f32_rows_per_block(int64_t groups, int64_t rows_per_group, int64_t keys) {
   return groups * ((rows_per_group + 31) / 32) < 256 && keys > 16 * kAttnF32Waves ? 16 : 32;
 }
@@ -194,7 +197,8 @@ constexpr bool attn_f32_one_wave(int64_t groups, int64_t rows_per_group, int64_t
 // Workgroups per row block.  With 16 rows and at most half a workgroup per
 // compute unit two share a block: each computes all of the scores and half of
 // the value products, three quarters of the work on twice the units (D = 128;
-// at D = 64 half a row is less than the lanes' 16-byte pieces).
+// at D = 64 half a row is less than the lanes' 16-byte pieces).  1000 keys, 128
+// blocks, shared and not: 26.5 and 33.4 us; 256 blocks, 64 keys 13.3 and 9.5.
 constexpr int attn_f32_row_parts(int head_dim, int rows_per_block, int64_t blocks) {
   return head_dim == 128 && rows_per_block == 16 && blocks <= 128 ? 2 : 1;
 }
@@ -227,8 +231,15 @@ constexpr size_t kConfXResidentBytes = (size_t)3 << 20;
 constexpr int conf_tile_rows(int n_rows) { return n_rows <= kConfSmallMaxRows ? kConfSmallBR : kConfBR; }
 
 // float32 path: tiles of 64 rows x 128 vocab ids, or of 32 rows x 256 ids where
-// that is all the rows (half of a 64-row tile would be padding).
-constexpr int kConfF32MinIds = 128;  // ids a workgroup gets at least
+// that is all the rows (half of a 64-row tile would be padding: 1 to 32 rows x
+// 1024 against 151936 ids 172-187 us, 226-230 with 64-row tiles; 64 rows against
+// 32000 ids 88 with 32-row tiles, 78 with 64).
+// Ids that a workgroup's share is aimed at: the groups are split to that, rounded
+// up, and the 32-id blocks are then divided evenly, so that a share may be as
+// little as half of it or a little more.  64 rows x 1024, aims of 64, 128, 256 and
+// 512 ids: 32000 ids 54, 79, 114, 191 us (at 128 a share is 133 ids, two tiles),
+// 8000 ids 49, 48, 112, 190; with 151936 ids, 594 a share, no difference.
+constexpr int kConfF32MinIds = 128;
 constexpr int conf_f32_tile_rows(int n_rows) { return n_rows <= 32 ? 32 : 64; }
 
 hipError_t launch_slot_attn_bf16(const AttnParams& p, int head_dim, hipStream_t stream);

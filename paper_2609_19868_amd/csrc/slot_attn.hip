@@ -389,7 +389,8 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(D ==
   // loop, so that every fragment address is a register set up once plus an
   // immediate offset (the 40 additions per tile it saves are a tenth of the
   // vector instructions beside the MFMAs, and the two hardly overlap: the 4B
-  // shape 295 -> 282 us, the training layout 645 -> 626 us).
+  // shape 308 -> 294 us, the training layout 672 -> 651, 1.7B 118 -> 115.5; at
+  // 0.6B, 42.1 us, no difference).
   // a wave of padding rows only helps to load the tiles (520 rows a group in
   // blocks of 128, Mode A: the step 211 -> 207 us)
   const bool live = rb * RB + wave_u * 32 < p.R;
