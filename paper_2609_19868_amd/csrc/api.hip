@@ -105,13 +105,18 @@ AttnPlan plan_attn(const zarya_slot_attn_desc* d) {
   // Few of them: twice as many 128-row blocks instead, which fill the units
   // with half the splits and give each row the result that eight splits of
   // 256-row blocks give, bit for bit.  Up to 32 key tiles a split (16 at D = 64,
-  // whose tiles are half as long); past that the second wave of a SIMD pays.
-  // One sequence, 32/8 heads x 128 tokens, D = 128, against 16 splits of 256-row
-  // blocks: 64 tiles 27.6 and 30.7 us, 128 33.3 and 36.9, 256 52.5 and 52.7,
-  // 384 71.0 and 68.5, 512 99.9 and 83.3; 16/8 heads, 512 tiles 55.0 and 56.9,
-  // 1024 99 and 95; D = 64, 16/8 heads: 128 tiles 20.3 and 22.1, 512 41.0 and 37.8
-  if (wide && groups * n_wide <= 16)
-    wide = (int64_t)pl.n_prefix_tiles * 4 > d->head_dim * (kAttnTargetWGs / (groups * n_narrow));
+  // whose tiles are half as long); past that the second wave of a SIMD pays, and
+  // sooner where the second blocks are partly empty, by their filled share.
+  // Against up to 32 splits of 256-row blocks, D = 128, one sequence of 32/8
+  // heads x 128 tokens: 64 tiles 27.6 and 30.7 us, 128 33.3 and 36.9, 256 52.5 and
+  // 52.7, 384 71.0 and 68.5, 512 99.9 and 83.3; two of 16/8 heads x 72 tokens (an
+  // eighth of the second blocks): 32 tiles 20.4 and 22.4, 128 32.2 and 31.1, 256
+  // 50.2 and 43.4; D = 64, one of 16/8 heads x 128: 128 tiles 20.3 and 22.1, 512
+  // 41.0 and 37.8
+  if (wide && groups * n_wide <= 16) {
+    const int64_t half = (int64_t)kAttnRowsPerBlock * n_wide;  // rows of the first (full) blocks
+    wide = pl.n_prefix_tiles * 4 * half > d->head_dim * (kAttnTargetWGs / (groups * n_narrow)) * (pl.R - half);
+  }
   pl.rows_per_block = wide ? kAttnWideRowsPerBlock : kAttnRowsPerBlock;
   pl.n_rb = wide ? n_wide : n_narrow;
   int ns = 1;

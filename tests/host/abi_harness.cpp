@@ -207,6 +207,8 @@ static void named_plans() {
       {"qwen4b batch 1", 1, 32, 8, 16384, 8, 16, 0, 128, 4, 8},
       {"qwen4b batch 1, 8192 keys", 1, 32, 8, 8192, 8, 16, 0, 128, 4, 8},
       {"qwen4b batch 1, 32768 keys: 64 tiles a split", 1, 32, 8, 32768, 8, 16, 0, 256, 2, 16},
+      {"16/8 heads x 72 tokens, batch 2, 32 tiles: 4 a split", 2, 16, 8, 2048, 8, 9, 0, 128, 2, 8},
+      {"16/8 heads x 72 tokens, batch 2, 33 tiles", 2, 16, 8, 2112, 8, 9, 0, 256, 1, 7},
       {"qwen4b batch 2", 2, 32, 8, 16384, 8, 16, 0, 256, 2, 8},
       // more than eight splits where they take three tiles off the longest walk
       {"qwen0.6b batch 1, 36 tiles", 1, 16, 8, 2304, 8, 8, 0, 128, 1, 8},
