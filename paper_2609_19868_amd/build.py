@@ -92,6 +92,8 @@ def build(verbose: bool = False) -> str:
     with cf.ThreadPoolExecutor(max_workers=min(8, len(sources))) as ex:
         outs = list(ex.map(lambda so: _run([hipcc, *HIPCC_FLAGS, RESOURCE_FLAG, "-c", so[0], "-o", so[1]]),
                            zip(sources, objs)))
+    if not any(map(kernel_resources, outs)):
+        raise RuntimeError(f"the compiler reported no kernel resources ({RESOURCE_FLAG})")
     for o in outs:
         check_kernels(o)
     tmp = LIB_PATH + ".tmp"
