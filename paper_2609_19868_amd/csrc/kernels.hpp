@@ -46,7 +46,7 @@ struct AttnParams32 {
   int pass, cross;
   float scale;
   int rows_total;
-  int item0, n_items;  // work items of this launch (set by the launcher)
+  int item0;  // first work item of this launch (set by the launcher)
 };
 
 // LM-head confidence.  Partials are per (vocab group, row): m = max logit,

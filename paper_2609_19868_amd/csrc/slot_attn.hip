@@ -573,7 +573,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   __shared__ float part_m[NW][RB], part_l[NW][RB];
 
   const int n_rb = (p.G * p.T + RB - 1) / RB;
-  const int w = xcd_work_index(blockIdx.x, gridDim.x >> 3, p.n_items) + p.item0;
+  const int w = xcd_work_index(blockIdx.x, gridDim.x >> 3, min(p.B * p.Hkv * n_rb * DS - p.item0, kAttnMaxGrid)) + p.item0;
   if (w < p.item0) return;
   const int d0 = (w % DS) * DO;  // first element taken
   const int rb = w / DS % n_rb, bg = w / (DS * n_rb);
@@ -846,8 +846,8 @@ void launch_attn_f32_as(AttnParams32 p, int blocks, hipStream_t stream) {
   const int64_t items = (int64_t)DS * blocks;
   for (int64_t i = 0; i < items; i += kAttnMaxGrid) {
     p.item0 = (int)i;
-    p.n_items = (int)std::min<int64_t>(items - i, kAttnMaxGrid);
-    slot_attn_f32_kernel<D, NR, DS, NW><<<dim3(8 * ((p.n_items + 7) / 8)), dim3(NW * 64), 0, stream>>>(p);
+    const int n = (int)std::min<int64_t>(items - i, kAttnMaxGrid);
+    slot_attn_f32_kernel<D, NR, DS, NW><<<dim3(8 * ((n + 7) / 8)), dim3(NW * 64), 0, stream>>>(p);
   }
 }
 
