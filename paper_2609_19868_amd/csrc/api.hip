@@ -102,9 +102,9 @@ AttnPlan plan_attn(const zarya_slot_attn_desc* d) {
   const bool fits_wide = d->dtype == ZARYA_DTYPE_BF16 && 2 * n_wide <= n_narrow &&
                          (int64_t)pl.n_prefix_tiles * kAttnKeysPerTile >= pl.T;
   bool wide = fits_wide;
-  // Few of them: twice as many 128-row blocks instead, which fill the units
-  // with half the splits and give each row the result that eight splits of
-  // 256-row blocks give, bit for bit.  Up to 32 key tiles a split (16 at D = 64,
+  // Few of them, and the splits ours to choose: twice as many 128-row blocks
+  // instead, which fill the units with half the splits and give each row the
+  // result that eight splits of 256-row blocks give, bit for bit.  Up to 32 key tiles a split (16 at D = 64,
   // whose tiles are half as long); past that the second wave of a SIMD pays, and
   // sooner where the second blocks are partly empty, by their filled share.
   // Against up to 32 splits of 256-row blocks, D = 128, one sequence of 32/8
@@ -113,7 +113,7 @@ AttnPlan plan_attn(const zarya_slot_attn_desc* d) {
   // eighth of the second blocks): 32 tiles 20.4 and 22.4, 128 32.2 and 31.1, 256
   // 50.2 and 43.4; D = 64, one of 16/8 heads x 128: 128 tiles 20.3 and 22.1, 512
   // 41.0 and 37.8
-  if (wide && groups * n_wide <= 16) {
+  if (wide && groups * n_wide <= 16 && d->prefix_splits == 0) {
     const int64_t half = (int64_t)kAttnRowsPerBlock * n_wide;  // rows of the first (full) blocks
     wide = pl.n_prefix_tiles * 4 * half > d->head_dim * (kAttnTargetWGs / (groups * n_narrow)) * (pl.R - half);
   }

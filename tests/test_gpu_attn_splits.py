@@ -37,10 +37,13 @@ def test_many_splits(splits, head_dim):
 def test_few_wide_blocks_give_the_result_of_eight_splits(prefix):
     """One sequence whose 256-row blocks are few: the planner halves the blocks
     instead of doubling the splits, which leaves every bit as eight splits of
-    256-row blocks had it."""
+    256-row blocks have it (a call that names its splits keeps those blocks)."""
     dev = require_gpu()
     wl = W.WORKLOADS["qwen4b"].replace(batch=1, prefix_len=prefix, hidden=0, vocab=0, seed=94)
     xd, _ = attn_inputs_dev(wl, dev)
+    rows = [Z._lib.slot_attn_plan(Z.slot_attn_desc(xd["q"], xd["k_cache"], xd["k_slot"], wl.n_slots, wl.slot_len,
+                                                   prefix_splits=n))["rows_per_workgroup"] for n in (0, 8)]
+    assert rows == [128, 256]
     say(f"slot_attn one sequence, {prefix} keys, planner's splits and eight")
     got = [Z.slot_attn(xd["q"], xd["k_cache"], xd["v_cache"], xd["k_slot"], xd["v_slot"], wl.n_slots, wl.slot_len,
                        prefix_len=wl.prefix_len, prefix_splits=n) for n in (0, 8)]

@@ -59,8 +59,9 @@ SMALL_BF16 = [
     # one key past a tile, and slots longer than several key tiles
     ("p65_long_slots", dict(batch=1, n_q_heads=2, n_kv_heads=1, prefix_len=65, n_slots=2, slot_len=200)),
     ("p1", dict(batch=3, n_q_heads=2, n_kv_heads=2, prefix_len=1, n_slots=3, slot_len=4)),
-    # 256-row (eight-wave) workgroups: two of them, the second with 112 padding rows; D = 64;
-    # and 260 rows, which stay on three 128-row workgroups
+    # rows that fit 256-row (eight-wave) workgroups, of which so few are taken as twice the
+    # 128-row ones (400 rows, 256 rows at D = 64; test_gpu_attn_padding.py has enough of them);
+    # and 260 rows, which do not
     ("wide_two_blocks", dict(batch=2, n_q_heads=8, n_kv_heads=2, prefix_len=333, n_slots=10, slot_len=10)),
     ("d64_wide", dict(batch=1, n_q_heads=8, n_kv_heads=2, head_dim=64, prefix_len=300, n_slots=8, slot_len=8)),
     ("g2_three_row_blocks", dict(batch=1, n_q_heads=4, n_kv_heads=2, prefix_len=190, n_slots=10, slot_len=13)),
