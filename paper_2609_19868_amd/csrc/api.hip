@@ -104,9 +104,10 @@ AttnPlan plan_attn(const zarya_slot_attn_desc* d) {
   bool wide = fits_wide;
   // Few of them, and the splits ours to choose: twice as many 128-row blocks
   // instead, which fill the units with half the splits and give each row the
-  // result that eight splits of 256-row blocks give, bit for bit.  Up to 32 key tiles a split (16 at D = 64,
-  // whose tiles are half as long); past that the second wave of a SIMD pays, and
-  // sooner where the second blocks are partly empty, by their filled share.
+  // result that eight splits of 256-row blocks give, bit for bit.  Up to 32 key
+  // tiles a split (16 at D = 64, whose tiles are half as long); past that the
+  // second wave of a SIMD pays, and sooner where the second blocks are partly
+  // empty, by their filled share.
   // Against up to 32 splits of 256-row blocks, D = 128, one sequence of 32/8
   // heads x 128 tokens: 64 tiles 27.6 and 30.7 us, 128 33.3 and 36.9, 256 52.5 and
   // 52.7, 384 71.0 and 68.5, 512 99.9 and 83.3; two of 16/8 heads x 72 tokens (an
